@@ -169,6 +169,18 @@ struct Ppm {
   T Rprev;    // right face value of cell k-3
 };
 
+// binary32: the recurrence carries differences from the cell values instead
+// of interface values (see ppm_push below).
+template <>
+struct Ppm<float> {
+  float qa, qb;  // q[k-2], q[k-1]
+  float qz, qy;  // q[k-3], q[k-4]
+  float dA;      // q[k-1] - q[k-2]
+  float dmA;     // twice the limited slope of cell k-2
+  float clA;     // q[k-2] minus the interface value between k-3 and k-2
+  float Rprev;   // right face value of cell k-3
+};
+
 // Limited slope of cell j from q[j-1], q[j], q[j+1].
 template <typename T>
 __device__ __forceinline__ T limited_slope(T qm, T q0, T qp) {
@@ -225,6 +237,58 @@ __device__ __forceinline__ void ppm_push(Ppm<T>& s, T qn, int k, T& UL, T& UR) {
   s.qb = qn;
 }
 
+// binary32.  The median of x, y and 0 is the smaller of x and y in magnitude
+// where their signs agree and 0 where they do not: the limiter's minimum and
+// its sign test in one v_med3_f32.  With dl, dr the differences to the two
+// neighbours and dq half their span, the limited slope is
+// med(dq, 2 med(dl, dr, 0), 0); here doubled, so that dq needs no halving.
+__device__ __forceinline__ float med0(float x, float y) {
+  return __builtin_amdgcn_fmed3f(x, y, 0.0f);
+}
+__device__ __forceinline__ float limited_slope2(float d, float dl, float dr) {
+  return med0(d, 4.0f * med0(dl, dr));
+}
+
+// The monotonised parabola likewise: with cl = c - l and rc = r - c, the
+// Colella-Woodward rules (flatten where l and r lie on one side of c, else
+// keep each end within twice the other's distance) are
+// l = c - med(cl, 2 rc, 0) and r = c + med(rc, 2 cl, 0).  cl and rc come
+// straight from the differences, rc = dr/2 - (dm_r - dm_c)/6 in one FMA, so
+// the ends carry the rounding of a difference and of one addition; the form
+// on interface values rounds the mean of two cell values first.  14
+// instructions per value instead of about 45 with compares and selects:
+// with the fused face flux below, the later-stage substep of 65,535 leaves
+// and 11 fields went from 2.89 to 2.24 ms, 5,832 leaves of 7 fields from 284
+// to 142 us, the 3D step of 6,966 leaves and 8 fields from 2.16 to 1.44 ms.
+__device__ __forceinline__ void ppm_push(Ppm<float>& s, float qn, int k, float& UL, float& UR) {
+  constexpr float C6 = (float)(1.0 / 6.0);
+  float dn = 0.0f, dm_new = 0.0f, rc = 0.0f, cl_new = 0.0f, Lc = 0.0f, Rc = 0.0f;
+  if (k >= 1) dn = qn - s.qb;
+  if (k >= 2) dm_new = limited_slope2(qn - s.qa, s.dA, dn);
+  if (k >= 3) {
+    // twice r - c of cell k-2; the same interface seen from cell k-1
+    const float rc2 = fmaf(-C6, dm_new - s.dmA, s.dA);
+    rc = 0.5f * rc2;
+    cl_new = s.dA - rc;
+    if (k >= 4) {
+      Lc = s.qa - med0(s.clA, rc2);
+      Rc = s.qa + med0(rc, s.clA + s.clA);
+    }
+  }
+  if (k >= 5) {
+    UL = s.Rprev;
+    UR = Lc;
+  }
+  s.Rprev = Rc;
+  s.clA = cl_new;
+  s.dmA = dm_new;
+  s.dA = dn;
+  s.qy = s.qz;
+  s.qz = s.qa;
+  s.qa = s.qb;
+  s.qb = qn;
+}
+
 // ---------------------------------------------------------------------------
 // EOS and Kurganov-Tadmor flux
 // ---------------------------------------------------------------------------
@@ -251,6 +315,60 @@ __device__ __forceinline__ bool eos(const Phys<T>& ph, T rho, T sx, T sy, T sz, 
   p = ph.gm1 * ei;
   c = sqrt(ph.gamma * p * rinv);
   return !(rho > T(0)) || !(p > T(0));
+}
+
+// binary32, both sides of a face: 1/rho from the hardware reciprocal and one
+// Newton step, the root from the hardware reciprocal root and one residual
+// step, each within a rounding of the exact value.  Where rho or c^2 of either
+// side is not in [2^-96, 2^96] (zero, negative, infinite, NaN or far from one)
+// or the dual-energy switch applies, the lane takes IEEE division, root and
+// the tracer's energy in the branch; only such a lane can hold an unphysical
+// state, so the test for one is made there.
+struct EosPair {
+  float riL, pL, cL, riR, pR, cR;
+};
+constexpr uint32_t F32_LO = 0x0F800000u, F32_SPAN = 0x60000000u;  // 2^-96, up to 2^96
+
+__device__ __forceinline__ float recip_newton(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, r, 1.0f), r, r);
+}
+__device__ __forceinline__ float sqrt_residual(float x) {
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float s = x * y;
+  return fmaf(fmaf(-s, s, x), 0.5f * y, s);
+}
+__device__ __forceinline__ EosPair eos_pair(const Phys<float>& ph, const float (&UL)[NF_CORE],
+                                            const float (&UR)[NF_CORE], bool& bad) {
+  EosPair e;
+  e.riL = recip_newton(UL[0]);
+  e.riR = recip_newton(UR[0]);
+  const float ssL = fmaf(UL[3], UL[3], fmaf(UL[2], UL[2], UL[1] * UL[1]));
+  const float ssR = fmaf(UR[3], UR[3], fmaf(UR[2], UR[2], UR[1] * UR[1]));
+  const float eL = fmaf(-0.5f * ssL, e.riL, UL[4]);
+  const float eR = fmaf(-0.5f * ssR, e.riR, UR[4]);
+  e.pL = ph.gm1 * eL;
+  e.pR = ph.gm1 * eR;
+  const float xL = ph.gamma * e.pL * e.riL, xR = ph.gamma * e.pR * e.riR;
+  e.cL = sqrt_residual(xL);
+  e.cR = sqrt_residual(xR);
+  const uint32_t far = max(max(__float_as_uint(UL[0]) - F32_LO, __float_as_uint(UR[0]) - F32_LO),
+                           max(__float_as_uint(xL) - F32_LO, __float_as_uint(xR) - F32_LO));
+  if (far > F32_SPAN || eL < ph.eta1 * UL[4] || eR < ph.eta1 * UR[4]) {
+    bad |= eos(ph, UL[0], UL[1], UL[2], UL[3], UL[4], UL[5], e.riL, e.pL, e.cL);
+    bad |= eos(ph, UR[0], UR[1], UR[2], UR[3], UR[4], UR[5], e.riR, e.pR, e.cR);
+  }
+  return e;
+}
+
+// Kurganov-Tadmor flux of one passive field from the face's normal
+// velocities and half its signal speed.
+template <typename T>
+__device__ __forceinline__ T passive_flux(T ul, T ur, T vl, T vr, T ha) {
+  if constexpr (sizeof(T) == 4)
+    return fmaf(-ha, ur - ul, 0.5f * fmaf(ul, vl, ur * vr));
+  else
+    return T(0.5) * (ul * vl + ur * vr) - ha * (ur - ul);
 }
 
 // ---------------------------------------------------------------------------
@@ -621,6 +739,32 @@ __device__ __forceinline__ void core_flux(const Phys<T>& ph, int d, const T (&UL
   for (int f = 0; f < NF_CORE; ++f) H[f] = T(0.5) * (FL[f] + FR[f]) - ha * (UR[f] - UL[f]);
 }
 
+// binary32: the same flux with the products and sums of each field fused,
+// H = (UL vL + UR vR)/2 - ha (UR - UL), the halves taken into the velocities.
+__device__ __forceinline__ void core_flux(const Phys<float>& ph, int d,
+                                          const float (&UL)[NF_CORE],
+                                          const float (&UR)[NF_CORE], float (&H)[NF_CORE],
+                                          float& vL, float& vR, float& ha, bool& bad) {
+  const EosPair e = eos_pair(ph, UL, UR, bad);
+  const float snL = d == 0 ? UL[1] : (d == 1 ? UL[2] : UL[3]);
+  const float snR = d == 0 ? UR[1] : (d == 1 ? UR[2] : UR[3]);
+  vL = snL * e.riL;
+  vR = snR * e.riR;
+  ha = 0.5f * fmaxf(fabsf(vL) + e.cL, fabsf(vR) + e.cR);
+  const float hL = 0.5f * vL, hR = 0.5f * vR;
+  const float hp = 0.5f * (e.pL + e.pR);
+  H[0] = 0.5f * (snL + snR);
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    const float f = fmaf(UL[1 + m], hL, UR[1 + m] * hR);
+    H[1 + m] = m == d ? f + hp : f;
+  }
+  H[4] = fmaf(UL[4] + e.pL, hL, (UR[4] + e.pR) * hR);
+  H[5] = fmaf(UL[5], hL, UR[5] * hR);
+#pragma unroll
+  for (int f = 0; f < NF_CORE; ++f) H[f] = fmaf(-ha, UR[f] - UL[f], H[f]);
+}
+
 // Stage combination of one cell: t = Uk + dt L with L = -sum * inv_dx, then
 // t (first stage) or U0 + beta (t - U0); u0 is the cell's U0 value, loaded
 // by the caller ahead of time.
@@ -705,6 +849,17 @@ __device__ __forceinline__ void stream_prologue(Ppm<T> (&st)[NF], const Sources&
   }
 }
 
+// Pins the recurrence values a push has just made (see keep_order).
+template <typename T>
+__device__ __forceinline__ void pin_state(Ppm<T>& st) {
+  keep_order(st.Rprev);
+  if constexpr (sizeof(T) == 4)
+    keep_order(st.clA);
+  else
+    keep_order(st.qfA);
+  keep_order(st.dmA);
+}
+
 // A steady stream step: feed the next value of every field and evaluate the
 // face between stream cells k-3 and k-2 (fluxes in H).  The core fields are
 // reconstructed first and give the face's velocities and signal speed; each
@@ -719,9 +874,7 @@ __device__ __forceinline__ void stream_step(const Phys<T>& ph, int d, Ppm<T> (&s
     ppm_push(st[f], qn[f], 5, core_L[f], core_R[f]);
     keep_order(core_L[f]);
     keep_order(core_R[f]);
-    keep_order(st[f].Rprev);
-    keep_order(st[f].qfA);
-    keep_order(st[f].dmA);
+    pin_state(st[f]);
     OCTOHYDRO_FENCE();
   }
   core_flux(ph, d, core_L, core_R, Hc, vL, vR, ha, bad);
@@ -738,11 +891,9 @@ __device__ __forceinline__ void stream_step(const Phys<T>& ph, int d, Ppm<T> (&s
     OCTOHYDRO_FENCE();
     T ul, ur;
     ppm_push(st[f], qn[f], 5, ul, ur);
-    H[f] = T(0.5) * (ul * vL + ur * vR) - ha * (ur - ul);
+    H[f] = passive_flux(ul, ur, vL, vR, ha);
     keep_order(H[f]);
-    keep_order(st[f].Rprev);
-    keep_order(st[f].qfA);
-    keep_order(st[f].dmA);
+    pin_state(st[f]);
   }
 }
 
@@ -777,7 +928,7 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
   double Hprev[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    st[f] = Ppm<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    st[f] = Ppm<T>{};
     Hprev[f] = 0.0;
   }
   stream_prologue<T, NF>(st, S, p, 0);
@@ -835,7 +986,7 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
   double Hprev[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    st[f] = Ppm<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    st[f] = Ppm<T>{};
     Hprev[f] = 0.0;
   }
   stream_prologue<T, NF>(st, S, p, k0);
@@ -1078,7 +1229,7 @@ __device__ __forceinline__ void group_step(const Phys<T>& ph, int d, Ppm<T> (&st
     const T vL = spd[slot].v[0][lane], vR = spd[slot].v[1][lane], ha = spd[slot].v[2][lane];
 #pragma unroll
     for (int f = 0; f < NG; ++f)
-      H[f] = T(0.5) * (ul[f] * vL + ur[f] * vR) - ha * (ur[f] - ul[f]);
+      H[f] = passive_flux(ul[f], ur[f], vL, vR, ha);
   }
 }
 
@@ -1108,7 +1259,7 @@ __device__ __forceinline__ void phase_xy_group(const StepArgs& s, const Phys<T>&
   double Hprev[NG];
 #pragma unroll
   for (int f = 0; f < NG; ++f) {
-    st[f] = Ppm<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    st[f] = Ppm<T>{};
     Hprev[f] = 0.0;
   }
   prologue_group<T, F0, NG>(st, S, p, 0);
@@ -1164,7 +1315,7 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
   double Hprev[NG];
 #pragma unroll
   for (int f = 0; f < NG; ++f) {
-    st[f] = Ppm<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    st[f] = Ppm<T>{};
     Hprev[f] = 0.0;
   }
   prologue_group<T, F0, NG>(st, S, p, k0);

@@ -46,6 +46,22 @@ __device__ __forceinline__ void parabola(const T* __restrict__ t, int s, T& l, T
   monotonise(q2, l, r);
 }
 
+// binary32: the ends from the differences of the five values (see ppm_push);
+// walking the line the other way changes the sign of every difference and
+// exchanges l and r, so it gives the same two values too.
+__device__ __forceinline__ void parabola(const float* __restrict__ t, int s, float& l, float& r) {
+  constexpr float C6 = (float)(1.0 / 6.0);
+  const float q0 = t[-2 * s], q1 = t[-s], q2 = t[0], q3 = t[s], q4 = t[2 * s];
+  const float d0 = q1 - q0, d1 = q2 - q1, d2 = q3 - q2, d3 = q4 - q3;
+  const float m1 = limited_slope2(q2 - q0, d0, d1);
+  const float m2 = limited_slope2(q3 - q1, d1, d2);
+  const float m3 = limited_slope2(q4 - q2, d2, d3);
+  // twice c - l and twice r - c
+  const float cl2 = fmaf(C6, m2 - m1, d1), rc2 = fmaf(-C6, m3 - m2, d2);
+  l = q2 - med0(0.5f * cl2, rc2);
+  r = q2 + med0(0.5f * rc2, cl2);
+}
+
 // One end of the PPM parabola of the cell at t along a line of tile stride s.
 template <typename T>
 __device__ __forceinline__ T line_end(const T* __restrict__ t, int s, bool right) {
@@ -127,7 +143,7 @@ __device__ __forceinline__ void face_flux_3d(const Phys<T>& ph, const T* __restr
       const PointLine pr = face_point<D>(-1, PU[q], PV[q]);
       const T ul = line_end(Gt + f * fsG + tl, pl.s, pl.right);
       const T ur = line_end(Gt + f * fsG + tr, pr.s, pr.right);
-      h[q] = T(0.5) * (ul * vl[q] + ur * vr[q]) - ha[q] * (ur - ul);
+      h[q] = passive_flux(ul, ur, vl[q], vr[q], ha[q]);
     }
     H[f] = simpson9(h);
     keep_order(H[f]);
@@ -600,13 +616,6 @@ __device__ __forceinline__ T prev_cell(T v) {
   } else {
     return __shfl_up(v, 8, 64);
   }
-}
-
-// Kurganov-Tadmor flux of one passive field at a point from the point's
-// velocities and half signal speed.
-template <typename T>
-__device__ __forceinline__ T passive_flux(T ul, T ur, T vl, T vr, T ha) {
-  return T(0.5) * (ul * vl + ur * vr) - ha * (ur - ul);
 }
 
 // Plane task: faces 1..7 along x and along y of cell plane z into Hs, lane
