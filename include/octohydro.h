@@ -340,7 +340,7 @@ const char* hydro_last_error(void);
 
 /*
  * Launch options of the fused substep kernel for one (dtype, n_fields) pair;
- * the defaults are 1 wave per SIMD and the XCD remap on.  The autotuner
+ * the defaults follow the type and the field count.  The autotuner
  * (paper_2210_06437_amd/autotune.py) times the choices and records the
  * fastest; the Python binding applies its recorded choices at import.
  *   HYDRO_OPT_WAVES_PER_SIMD  1 or 2: register budget of the kernel (2 waves

@@ -449,12 +449,45 @@ struct Options {
   int fused_restrict = 1;
   int recon3d_wg = 2;
 };
-static Options g_opts[2][17];
+
+// Launch shape before any hydro_set_option, by what is alive in a wavefront.
+// Later-stage substep of 27,649 leaves, us, with one wavefront per leaf at one
+// or two per SIMD (512 or 256 registers) and with the species on a second
+// wavefront:
+//   binary64, fields  6: 939  963     -    10: 1812  1867  1673
+//                     7: 1337 1114 1457    11: 1971  2839  1797
+//                     8: 1502 1285 1516    14: 2558  7020  2214
+//                     9: 1676 1468 1588    15: 2861  8852  2483 (256 registers)
+//   binary32          9: 798   806  828    11: 1009  1009   941
+//                    10: 873   881  881    16: 1736  2154  1462
+// Up to the field count whose state fits 256 registers with few spills one
+// wavefront holds all fields; beyond it the second wavefront's barrier each
+// step costs less than the spills or the lower occupancy.  6 binary64 and all
+// binary32 counts need no cap: they stay below 256 registers by themselves.
+static Options default_options(int dtype, int nf) {
+  Options o;
+  if (dtype == HYDRO_F64) {
+    o.waves_per_leaf = nf >= 10 ? 2 : 1;
+    o.waves_per_simd = (nf >= 7 && nf <= 9) || nf >= 15 ? 2 : 1;
+  } else {
+    o.waves_per_leaf = nf >= 11 ? 2 : 1;
+  }
+  return o;
+}
+
+struct OptionTable {
+  Options o[2][17];
+  OptionTable() {
+    for (int dtype = 0; dtype < 2; ++dtype)
+      for (int nf = NF_CORE; nf <= 16; ++nf) o[dtype][nf] = default_options(dtype, nf);
+  }
+};
+static OptionTable g_opts;
 static std::mutex g_opts_mu;
 
 static Options get_options(int dtype, int nf) {
   std::lock_guard<std::mutex> lk(g_opts_mu);
-  return g_opts[dtype][nf];
+  return g_opts.o[dtype][nf];
 }
 
 // Whether the step kernel itself leaves the CFL minimum of its output: the
@@ -719,7 +752,7 @@ int hydro_set_option(int32_t dtype, int32_t n_fields, int32_t option, int32_t va
   if ((dtype != HYDRO_F64 && dtype != HYDRO_F32) || n_fields < NF_CORE || n_fields > 16)
     return fail(HYDRO_E_ARG, "hydro_set_option: bad dtype %d or n_fields %d", dtype, n_fields);
   std::lock_guard<std::mutex> lk(g_opts_mu);
-  Options& o = g_opts[dtype][n_fields];
+  Options& o = g_opts.o[dtype][n_fields];
   switch (option) {
     case HYDRO_OPT_WAVES_PER_SIMD:
       if (value != 1 && value != 2)

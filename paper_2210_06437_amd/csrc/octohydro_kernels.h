@@ -164,7 +164,7 @@ template <typename T>
 struct Ppm {
   T qa, qb;   // q[k-2], q[k-1]
   T qz, qy;   // q[k-3], q[k-4]
-  T dmA;      // limited slope of cell k-2
+  T dmA;      // half the limited slope of cell k-2
   T qfA;      // interface value between cells k-3 and k-2
   T Rprev;    // right face value of cell k-3
 };
@@ -181,44 +181,62 @@ struct Ppm<float> {
   float Rprev;   // right face value of cell k-3
 };
 
-// Limited slope of cell j from q[j-1], q[j], q[j+1].
-template <typename T>
-__device__ __forceinline__ T limited_slope(T qm, T q0, T qp) {
-  const T dq = T(0.5) * (qp - qm);
-  const T dl = q0 - qm;
-  const T dr = qp - q0;
-  // min(2|dl|, 2|dr|) evaluated as 2 min(|dl|, |dr|): scaling by 2 is exact
-  // and monotone, so both give the same bits
-  const T lim = fmin(fabs(dq), T(2) * fmin(fabs(dl), fabs(dr)));
-  return (dl * dr > T(0)) ? copysign(lim, dq) : T(0);
+// Half the limited slope of cell j from q[j-1], q[j], q[j+1].  The slope is
+// the centred difference, limited to twice the smaller one-sided difference,
+// where those agree in sign, else 0: the centred difference clamped to
+// [2 min(max(dl, dr), 0), 2 max(min(dl, dr), 0)].  Everything is scaled by a
+// quarter of the full span, and scaling by powers of two is exact, so the
+// value is the limiter's own, bit for bit, with no sign test or select.
+__device__ __forceinline__ double half_slope(double qm, double q0, double qp) {
+  const double d4 = 0.25 * (qp - qm);
+  const double dl = q0 - qm, dr = qp - q0;
+  const double hi = fmax(fmin(dl, dr), 0.0), lo = fmin(fmax(dl, dr), 0.0);
+  return fmin(fmax(d4, lo), hi);
 }
 
-// Monotonised parabola of a cell with centre value c and face values l, r.
-template <typename T>
-__device__ __forceinline__ void monotonise(T c, T& l, T& r) {
-  const T dlr = r - l;
-  const T a6 = T(6) * (c - T(0.5) * (l + r));
-  const T lo = T(3) * c - T(2) * r;
-  const T ro = T(3) * c - T(2) * l;
-  const bool flat = (r - c) * (c - l) <= T(0);
-  const bool fix_l = dlr * a6 > dlr * dlr;
-  const bool fix_r = -(dlr * dlr) > dlr * a6;
-  // fix_l and fix_r exclude each other (dlr^2 >= 0, and a NaN makes both
-  // false), so the right value needs no test of fix_l
-  const T nl = flat ? c : (fix_l ? lo : l);
-  const T nr = flat ? c : (fix_r ? ro : r);
-  l = nl;
-  r = nr;
+// Interface value between cells of values a and b with half slopes ha, hb:
+// (a + b)/2 - (dm_b - dm_a)/6.  The halved sum is exact, so the FMA rounds
+// once, as the subtraction does.
+__device__ __forceinline__ double interface_value(double a, double b, double ha, double hb) {
+  return fma(0.5, a + b, -((hb - ha) * (2.0 * (1.0 / 6.0))));
+}
+
+// Monotonised parabola of a cell with centre value c and face values l, r:
+// l = 3c - 2r where (r - l) a6 > (r - l)^2, r = 3c - 2l where it is below
+// -(r - l)^2 (the two exclude each other), both c where c is no interior
+// point of [l, r].  Each replacement is written under its own execution
+// mask: a 64-bit select is two instructions a value, a masked move or FMA
+// one, so this takes 7 instructions where selects took 13.
+__device__ __forceinline__ void monotonise(double c, double& l, double& r) {
+  const double dlr = r - l;
+  const double e1 = dlr * (6.0 * fma(-0.5, l + r, c)), e2 = dlr * dlr;
+  const double c3 = 3.0 * c;
+  const double in = (r - c) * (c - l);
+  uint64_t saved;
+  asm("s_mov_b64 %[sv], exec\n\t"
+      "v_cmpx_lt_f64_e64 vcc, %[e2], %[e1]\n\t"
+      "v_fma_f64 %[l], -2.0, %[r], %[c3]\n\t"
+      "s_mov_b64 exec, %[sv]\n\t"
+      "v_cmpx_lt_f64_e64 vcc, %[e1], -%[e2]\n\t"
+      "v_fma_f64 %[r], -2.0, %[l], %[c3]\n\t"
+      "s_mov_b64 exec, %[sv]\n\t"
+      "v_cmpx_ge_f64_e64 vcc, 0, %[in]\n\t"
+      "v_mov_b64 %[l], %[c]\n\t"
+      "v_mov_b64 %[r], %[c]\n\t"
+      "s_mov_b64 exec, %[sv]"
+      : [l] "+v"(l), [r] "+v"(r), [sv] "=&s"(saved)
+      : [c] "v"(c), [c3] "v"(c3), [e1] "v"(e1), [e2] "v"(e2), [in] "v"(in)
+      : "vcc");
 }
 
 // Feed the k-th value of a pencil stream; when k >= 5, returns the face
 // states of the face between stream cells k-3 and k-2 in (UL, UR).  k is a
 // compile-time constant after unrolling.
-template <typename T>
-__device__ __forceinline__ void ppm_push(Ppm<T>& s, T qn, int k, T& UL, T& UR) {
-  T dm_new = T(0), qf_new = T(0), Lc = T(0), Rc = T(0);
-  if (k >= 2) dm_new = limited_slope(s.qa, s.qb, qn);
-  if (k >= 3) qf_new = T(0.5) * (s.qa + s.qb) - (dm_new - s.dmA) * T(1.0 / 6.0);
+__device__ __forceinline__ void ppm_push(Ppm<double>& s, double qn, int k, double& UL,
+                                         double& UR) {
+  double dm_new = 0.0, qf_new = 0.0, Lc = 0.0, Rc = 0.0;
+  if (k >= 2) dm_new = half_slope(s.qa, s.qb, qn);
+  if (k >= 3) qf_new = interface_value(s.qa, s.qb, s.dmA, dm_new);
   if (k >= 4) {
     Lc = s.qfA;
     Rc = qf_new;
@@ -317,44 +335,83 @@ __device__ __forceinline__ bool eos(const Phys<T>& ph, T rho, T sx, T sy, T sz, 
   return !(rho > T(0)) || !(p > T(0));
 }
 
-// binary32, both sides of a face: 1/rho from the hardware reciprocal and one
-// Newton step, the root from the hardware reciprocal root and one residual
-// step, each within a rounding of the exact value.  Where rho or c^2 of either
-// side is not in [2^-96, 2^96] (zero, negative, infinite, NaN or far from one)
-// or the dual-energy switch applies, the lane takes IEEE division, root and
-// the tracer's energy in the branch; only such a lane can hold an unphysical
-// state, so the test for one is made there.
+// Equation of state of both sides of a face.  1/rho and the sound speed come
+// from the hardware reciprocal and reciprocal root, refined without the
+// scaling and special-case steps of the IEEE sequences: binary64 to the
+// correctly rounded value (two Newton steps and the residual correction of
+// Markstein; one Goldschmidt step and two residual corrections), binary32 to
+// within a rounding of it (one step each).  Where rho or c^2 of either side
+// lies outside the range that this serves (zero, negative, infinite, NaN or
+// very far from one) or the dual-energy switch applies, the lane takes IEEE
+// division, root and the tracer's energy in the branch; only such a lane can
+// hold an unphysical state, so the test for one is made there.
+template <typename T>
 struct EosPair {
-  float riL, pL, cL, riR, pR, cR;
+  T riL, pL, cL, riR, pR, cR;
 };
-constexpr uint32_t F32_LO = 0x0F800000u, F32_SPAN = 0x60000000u;  // 2^-96, up to 2^96
 
-__device__ __forceinline__ float recip_newton(float x) {
+__device__ __forceinline__ double recip_refined(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ float recip_refined(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(fmaf(-x, r, 1.0f), r, r);
 }
-__device__ __forceinline__ float sqrt_residual(float x) {
+__device__ __forceinline__ double sqrt_refined(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double s = x * y, h = 0.5 * y;
+  const double e = fma(-h, s, 0.5);
+  h = fma(h, e, h);
+  s = fma(s, e, s);
+  s = fma(fma(-s, s, x), h, s);
+  return fma(fma(-s, s, x), h, s);
+}
+__device__ __forceinline__ float sqrt_refined(float x) {
   const float y = __builtin_amdgcn_rsqf(x);
   const float s = x * y;
   return fmaf(fmaf(-s, s, x), 0.5f * y, s);
 }
-__device__ __forceinline__ EosPair eos_pair(const Phys<float>& ph, const float (&UL)[NF_CORE],
-                                            const float (&UR)[NF_CORE], bool& bad) {
-  EosPair e;
-  e.riL = recip_newton(UL[0]);
-  e.riR = recip_newton(UR[0]);
-  const float ssL = fmaf(UL[3], UL[3], fmaf(UL[2], UL[2], UL[1] * UL[1]));
-  const float ssR = fmaf(UR[3], UR[3], fmaf(UR[2], UR[2], UR[1] * UR[1]));
-  const float eL = fmaf(-0.5f * ssL, e.riL, UL[4]);
-  const float eR = fmaf(-0.5f * ssR, e.riR, UR[4]);
+
+// Distance of a value's leading word above that of the range's low end; an
+// unsigned value beyond FAST_SPAN for anything outside the range.  The range
+// is 2^-500..2^500 in binary64, 2^-96..2^96 in binary32.
+__device__ __forceinline__ uint32_t range_key(double x) {
+  return (uint32_t)((uint64_t)__double_as_longlong(x) >> 32) - 0x20B00000u;
+}
+__device__ __forceinline__ uint32_t range_key(float x) {
+  return __float_as_uint(x) - 0x0F800000u;
+}
+template <typename T>
+constexpr uint32_t FAST_SPAN = sizeof(T) == 8 ? 0x3E800000u : 0x60000000u;
+
+// Internal energy per volume E - s.s / (2 rho).
+__device__ __forceinline__ double internal_energy(const double (&U)[NF_CORE], double ri) {
+  const double ss = (U[1] * U[1] + U[2] * U[2]) + U[3] * U[3];
+  return fma(-0.5, ss * ri, U[4]);  // the halving is exact
+}
+__device__ __forceinline__ float internal_energy(const float (&U)[NF_CORE], float ri) {
+  const float ss = fmaf(U[3], U[3], fmaf(U[2], U[2], U[1] * U[1]));
+  return fmaf(-0.5f * ss, ri, U[4]);
+}
+
+template <typename T>
+__device__ __forceinline__ EosPair<T> eos_pair(const Phys<T>& ph, const T (&UL)[NF_CORE],
+                                               const T (&UR)[NF_CORE], bool& bad) {
+  EosPair<T> e;
+  e.riL = recip_refined(UL[0]);
+  e.riR = recip_refined(UR[0]);
+  const T eL = internal_energy(UL, e.riL), eR = internal_energy(UR, e.riR);
   e.pL = ph.gm1 * eL;
   e.pR = ph.gm1 * eR;
-  const float xL = ph.gamma * e.pL * e.riL, xR = ph.gamma * e.pR * e.riR;
-  e.cL = sqrt_residual(xL);
-  e.cR = sqrt_residual(xR);
-  const uint32_t far = max(max(__float_as_uint(UL[0]) - F32_LO, __float_as_uint(UR[0]) - F32_LO),
-                           max(__float_as_uint(xL) - F32_LO, __float_as_uint(xR) - F32_LO));
-  if (far > F32_SPAN || eL < ph.eta1 * UL[4] || eR < ph.eta1 * UR[4]) {
+  const T xL = ph.gamma * e.pL * e.riL, xR = ph.gamma * e.pR * e.riR;
+  e.cL = sqrt_refined(xL);
+  e.cR = sqrt_refined(xR);
+  const uint32_t far = max(max(range_key(UL[0]), range_key(UR[0])),
+                           max(range_key(xL), range_key(xR)));
+  if (far > FAST_SPAN<T> || eL < ph.eta1 * UL[4] || eR < ph.eta1 * UR[4]) {
     bad |= eos(ph, UL[0], UL[1], UL[2], UL[3], UL[4], UL[5], e.riL, e.pL, e.cL);
     bad |= eos(ph, UR[0], UR[1], UR[2], UR[3], UR[4], UR[5], e.riR, e.pR, e.cR);
   }
@@ -368,7 +425,7 @@ __device__ __forceinline__ T passive_flux(T ul, T ur, T vl, T vr, T ha) {
   if constexpr (sizeof(T) == 4)
     return fmaf(-ha, ur - ul, 0.5f * fmaf(ul, vl, ur * vr));
   else
-    return T(0.5) * (ul * vl + ur * vr) - ha * (ur - ul);
+    return fma(T(0.5), ul * vl + ur * vr, -(ha * (ur - ul)));  // the halving is exact
 }
 
 // ---------------------------------------------------------------------------
@@ -506,110 +563,132 @@ __device__ __forceinline__ void atomic_min_positive(double* out, double v, int l
               (unsigned long long)__double_as_longlong(v));
 }
 
-// Per-leaf constants.  Neighbour kinds and ids of the six face neighbours are
-// handed to the phases as plain values (the phase picks its axis once), so
-// no per-lane choice is ever made by indexing memory.
+// The lane number as a value the compiler knows nothing about, so that what a
+// phase derives from it (offsets, masks, addresses) is worked out in the phase
+// and dies with it.  Otherwise all of it is hoisted out of the loop over the
+// halves and held through every phase: about 100 registers.
+__device__ __forceinline__ int fresh(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// Per-leaf constants: coordinates and the six face neighbours (kind, id) in
+// the order -x, +x, -y, +y, -z, +z, all uniform over the wave and held in
+// scalar registers.
 struct LeafInfo {
   int leaf, blocks;
   int ix, iy, iz;
+  int kind[6], id[6];
 };
 
-// Face neighbour (kind, id) of a pencil axis, low and high side.
-struct FaceNbr {
-  int klo, ilo, khi, ihi;
-  int rlo, rhi;  // coarse register slot of the low / high face, or -1
-  int flo, fhi;  // fine register entry (slot << 2 | quadrant), or -1
-};
+__device__ __forceinline__ LeafInfo leaf_info(const GridArgs& g, int leaf) {
+  LeafInfo li = {};
+  li.leaf = leaf;
+  const int4 c4 = reinterpret_cast<const int4*>(g.coord)[leaf];
+  li.ix = __builtin_amdgcn_readfirstlane(c4.y);
+  li.iy = __builtin_amdgcn_readfirstlane(c4.z);
+  li.iz = __builtin_amdgcn_readfirstlane(c4.w);
+  li.blocks = g.base << __builtin_amdgcn_readfirstlane(c4.x);
+  // face-neighbour slots: -x 12, +x 14, -y 10, +y 16, -z 4, +z 22
+  constexpr int SLOT[6] = {12, 14, 10, 16, 4, 22};
+  const uint8_t* kd = g.kind + 27 * leaf;
+  const int32_t* nb = g.nbr + 27 * leaf;
+#pragma unroll
+  for (int o = 0; o < 6; ++o) {
+    li.kind[o] = __builtin_amdgcn_readfirstlane((int)kd[SLOT[o]]);
+    li.id[o] = __builtin_amdgcn_readfirstlane(nb[SLOT[o]]);
+  }
+  return li;
+}
 
-// Record the fluxes H (all fields) through face `face` (0 = low, 8 = high
-// face of the leaf) of a pencil at transverse position (u, v) of that face.
-template <typename T, int NF>
-__device__ __forceinline__ void record_face(const GridArgs& g, const FaceNbr& fn, int face, int u,
-                                            int v, const T (&H)[NF]) {
-  const int cs = face == 0 ? fn.rlo : fn.rhi;
-  const int fe = face == 0 ? fn.flo : fn.fhi;
+// Record the fluxes H of fields [F0, F0 + NG) through face `face` (0 = low, 8
+// = high face of the leaf) normal to axis d at transverse position (u, v).
+// The register slots are read here, not held: only two faces of a pencil are
+// recorded, and only on trees with the flux correction.
+template <typename T, int NF, int F0, int NG>
+__device__ __forceinline__ void record_faces(const GridArgs& g, int leaf, int d, int face, int u,
+                                             int v, const T* __restrict__ H) {
+  const int o = 6 * leaf + 2 * d + (face == 0 ? 0 : 1);
+  const int cs = g.face_slot[o], fe = g.fine_slot[o];
   if (cs >= 0) {
     double* r = g.reg + (size_t)cs * NF * REG_STRIDE + u + 8 * v;
 #pragma unroll
-    for (int f = 0; f < NF; ++f) r[f * REG_STRIDE] = (double)H[f];
+    for (int f = 0; f < NG; ++f) r[(F0 + f) * REG_STRIDE] = (double)H[f];
   }
   if (fe >= 0) {
     const int q = fe & 3;
     double* r = g.reg + (size_t)(fe >> 2) * NF * REG_STRIDE + REG_COARSE +
                 (8 * (q & 1) + u) + 16 * (8 * (q >> 1) + v);
 #pragma unroll
-    for (int f = 0; f < NF; ++f) r[f * REG_STRIDE] = (double)H[f];
+    for (int f = 0; f < NG; ++f) r[(F0 + f) * REG_STRIDE] = (double)H[f];
   }
 }
 
 // A lane's pencil along axis d through transverse cell (a, b): where each of
 // its 14 stream values comes from, as byte offsets into a field array.
-// Interior value k sits at off + (k-3) sd; each ghost value k in
-// {0,1,2,11,12,13} comes from gofs[] -- a same-level cell or the covering
-// coarse cell (injection) of the state, or, on a refined side (ref_lo /
-// ref_hi), a cell of the refined node's restricted copy.  The sources are the
-// same for every field, so they are worked out once per pencil.
-typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-
+// Interior value k is cell k-3 from `off`; a ghost value is cell l of the
+// neighbour block on its side, l in {5,6,7} below and {0,1,2} above: of a
+// same-level leaf or, on a refined side, of the refined node's restricted
+// copy (l cells from the base), or the covering cell of a coarser leaf (l >> 1
+// cells).  Two bases and a flag per side stand for the six ghost offsets.
 struct Pencil {
-  uint32_t off, sd;
-  u32x8 gofs;  // a vector value: selecting an entry never touches memory
-  bool ref_lo, ref_hi;
-  bool any_lo, any_hi;  // some lane of the wave has ref_lo (ref_hi)
+  uint32_t off, glo, ghi;
+  uint32_t sh;             // log2 of the byte stride along d
+  bool clo, chi;           // coarser neighbour below, above
+  bool ref_lo, ref_hi;     // refined neighbour
+  bool any_lo, any_hi;     // some lane of the wave has ref_lo (ref_hi)
 };
 
-// cd = the leaf's block coordinate along d.
-__device__ __forceinline__ uint32_t ghost_offset(const GridArgs& g, const LeafInfo& li, int kind,
-                                                 int id, int side, int d, int cd, int lx, int ly,
-                                                 int lz) {
-  if (kind == HYDRO_SAME_LEAF) return id * CELLS + lz * 64 + ly * 8 + lx;
-  if (kind == HYDRO_COARSER_LEAF) {
-    // the neighbour block along d, wrapped; transverse blocks are the leaf's
-    const int nb = wrap(cd + side, li.blocks);
-    const int bx = d == 0 ? nb : li.ix, by = d == 1 ? nb : li.iy, bz = d == 2 ? nb : li.iz;
-    return id * CELLS + (4 * (bz & 1) + (lz >> 1)) * 64 + (4 * (by & 1) + (ly >> 1)) * 8 +
-           (4 * (bx & 1) + (lx >> 1));
-  }
-  // refined neighbour: the coarse cell of the node's restricted copy
-  return id * CELLS + lz * 64 + ly * 8 + lx;
+// Byte offset of cell 0 along d of the neighbour block `id` on side `side`,
+// at transverse cells (a, b); tr is the leaf's own transverse offset and cd
+// its block coordinate along d, (ba, bb) those along the transverse axes.
+template <typename T>
+__device__ __forceinline__ uint32_t ghost_base(int kind, int id, int side, uint32_t tr, int cd,
+                                               int blocks, int a, int b, int ba, int bb, int d,
+                                               uint32_t sh) {
+  uint32_t o = (uint32_t)sizeof(T) * ((uint32_t)id * CELLS);
+  if (kind != HYDRO_COARSER_LEAF) return o + tr;
+  // the neighbour block along d, wrapped, is odd or even in its parent; the
+  // transverse blocks are the leaf's
+  const int nb = wrap(cd + side, blocks);
+  const int ca = 4 * (ba & 1) + (a >> 1), cb = 4 * (bb & 1) + (b >> 1);
+  o += (uint32_t)sizeof(T) * (d == 0 ? cb * 64 + ca * 8 : (d == 1 ? cb * 64 + ca : cb * 8 + ca));
+  return o + ((uint32_t)(4 * (nb & 1)) << sh);
 }
 
 template <typename T>
-__device__ __forceinline__ Pencil make_pencil(const GridArgs& g, const LeafInfo& li, int d, int a,
-                                              int b, const FaceNbr& fn) {
+__device__ __forceinline__ Pencil make_pencil(const LeafInfo& li, int d, int a, int b) {
   Pencil p;
-  constexpr uint32_t W = sizeof(T);
+  constexpr uint32_t W = sizeof(T), LW = sizeof(T) == 8 ? 3 : 2;
   // d = 0: (x, a=y, b=z); d = 1: (a=x, y, b=z); d = 2: (a=x, b=y, z)
-  p.off = W * (li.leaf * CELLS + (d == 0 ? b * 64 + a * 8 : (d == 1 ? b * 64 + a : b * 8 + a)));
-  p.sd = W * (d == 0 ? 1 : (d == 1 ? 8 : 64));
-  const int klo = fn.klo, ilo = fn.ilo, khi = fn.khi, ihi = fn.ihi;
+  const uint32_t tr = W * (uint32_t)(d == 0 ? b * 64 + a * 8 : (d == 1 ? b * 64 + a : b * 8 + a));
+  p.sh = LW + (d == 0 ? 0 : (d == 1 ? 3 : 6));
+  p.off = W * ((uint32_t)li.leaf * CELLS) + tr;
+  // the axis's values (d may differ between lanes) as arithmetic on values: a
+  // choice between the members became an indexed load from a scratch copy of
+  // the struct, with a full memory wait each
+  const int mx = d == 0, my = d == 1, mz = d == 2;
+  const int klo = mx * li.kind[0] + my * li.kind[2] + mz * li.kind[4];
+  const int khi = mx * li.kind[1] + my * li.kind[3] + mz * li.kind[5];
+  const int ilo = mx * li.id[0] + my * li.id[2] + mz * li.id[4];
+  const int ihi = mx * li.id[1] + my * li.id[3] + mz * li.id[5];
+  const int cd = mx * li.ix + my * li.iy + mz * li.iz;
+  const int ba = mx * li.iy + (1 - mx) * li.ix, bb = mz * li.iy + (1 - mz) * li.iz;
+  p.clo = klo == HYDRO_COARSER_LEAF;
+  p.chi = khi == HYDRO_COARSER_LEAF;
   p.ref_lo = klo == HYDRO_SAME_REFINED;
   p.ref_hi = khi == HYDRO_SAME_REFINED;
   // wave votes taken once per pencil, outside the streaming loops
   p.any_lo = __any(p.ref_lo);
   p.any_hi = __any(p.ref_hi);
-  // the block coordinate along d (d may differ between lanes), as arithmetic
-  // on values: a select between the LeafInfo fields became an indexed load
-  // from a scratch copy of it, with a full memory wait per ghost position
-  const int cd = (d == 0) * li.ix + (d == 1) * li.iy + (d == 2) * li.iz;
-#pragma unroll
-  for (int j = 0; j < 2 * GH; ++j) {
-    const bool hi = j >= GH;
-    const int l = hi ? j - GH : j + SUB - GH;  // cell along d inside the neighbour block
-    const int lx = d == 0 ? l : a;
-    const int ly = d == 0 ? a : (d == 1 ? l : b);
-    const int lz = d == 2 ? l : b;
-    p.gofs[j] =
-        W * ghost_offset(g, li, hi ? khi : klo, hi ? ihi : ilo, hi ? 1 : -1, d, cd, lx, ly, lz);
-  }
+  p.glo = ghost_base<T>(klo, ilo, -1, tr, cd, li.blocks, a, b, ba, bb, d, p.sh);
+  p.ghi = ghost_base<T>(khi, ihi, 1, tr, cd, li.blocks, a, b, ba, bb, d, p.sh);
   return p;
 }
 
 // Where stream position k (0..13) of a pencil comes from: a byte offset
-// into a field array and whether it is a refined ghost (mean of 8 cells).
-// Worked out once per stream step and shared by every field; for a step
-// index known only at run time the ghost offset is picked by a select chain
-// over the six values.
+// into a field array and whether it is a cell of a node copy.  Worked out
+// once per stream step and shared by every field.
 struct Src {
   uint32_t o;    // offset of the value in its array
   bool ref;      // this lane's value comes from a node copy
@@ -619,14 +698,19 @@ struct Src {
 __device__ __forceinline__ Src pencil_src(const Pencil& p, int k) {
   Src s;
   if (k >= GH && k < GH + SUB) {
-    s.o = p.off + (uint32_t)(k - GH) * p.sd;
+    s.o = p.off + ((uint32_t)(k - GH) << p.sh);
     s.ref = s.any_ref = false;
-    return s;
+  } else if (k < GH) {
+    const int l = k + SUB - GH;
+    s.o = p.glo + ((uint32_t)(p.clo ? l >> 1 : l) << p.sh);
+    s.ref = p.ref_lo;
+    s.any_ref = p.any_lo;
+  } else {
+    const int l = k - (GH + SUB);
+    s.o = p.ghi + ((uint32_t)(p.chi ? l >> 1 : l) << p.sh);
+    s.ref = p.ref_hi;
+    s.any_ref = p.any_hi;
   }
-  s.o = k == 0 ? p.gofs[0] : k == 1 ? p.gofs[1] : k == 2 ? p.gofs[2]
-      : k == 11 ? p.gofs[3] : k == 12 ? p.gofs[4] : p.gofs[5];
-  s.ref = k < GH ? p.ref_lo : p.ref_hi;
-  s.any_ref = k < GH ? p.any_lo : p.any_hi;
   return s;
 }
 
@@ -668,6 +752,16 @@ __device__ __forceinline__ float bload_once(float, const FieldView& v, uint32_t 
                             __builtin_amdgcn_raw_buffer_load_b32(v.r, (int)o, (int)v.fo, CACHE_NT));
 }
 
+__device__ __forceinline__ void bstore_once(double x, const FieldView& v, uint32_t o) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), v.r, (int)o, (int)v.fo,
+                                        CACHE_NT);
+}
+__device__ __forceinline__ void bstore_once(float x, const FieldView& v, uint32_t o) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), v.r, (int)o, (int)v.fo,
+                                        CACHE_NT);
+}
+
 // The two arrays stream values come from: the stage input (all interior and
 // same-level or coarser ghosts) and the restricted node copies (ghosts on a
 // refined side), each with its field stride in bytes.
@@ -681,6 +775,12 @@ __device__ __forceinline__ Sources make_sources(const void* Uk, const void* rsta
   return Sources{state_rsrc(Uk, (uint32_t)nf * uk_fs),
                  state_rsrc(rstate, rstate ? (uint32_t)nf * rn_fs : 0u), uk_fs, rn_fs};
 }
+
+// Ends the node-copy branch of the loads below with a statement of its own
+// (no instruction).  Without it the compiler may merge the two branches'
+// loads into one with a per-lane choice of the array, and runs each such load
+// in a loop over the distinct arrays.
+__device__ __forceinline__ void branches_apart() { asm volatile("; node copies"); }
 
 // The values of a stream position in all NF fields.  Where some lane of the
 // wave reads a node copy, the lanes read from two arrays: the lanes of each
@@ -696,6 +796,7 @@ __device__ __forceinline__ void load_position(const Sources& S, const Src& s, T 
     if (s.ref) {
 #pragma unroll
       for (int f = 0; f < NF; ++f) q[f] = bload(T(), FieldView{S.rn, f * S.rn_fs}, s.o);
+      branches_apart();
     } else {
 #pragma unroll
       for (int f = 0; f < NF; ++f) q[f] = bload(T(), FieldView{S.uk, f * S.uk_fs}, s.o);
@@ -709,34 +810,27 @@ __device__ __forceinline__ void load_position(const Sources& S, const Src& s, T 
 // Kurganov-Tadmor fluxes of the core fields at one face normal to axis d;
 // also returns the face's normal velocities and half the signal speed for
 // the passive species.
-template <typename T>
-__device__ __forceinline__ void core_flux(const Phys<T>& ph, int d, const T (&UL)[NF_CORE],
-                                          const T (&UR)[NF_CORE], T (&H)[NF_CORE], T& vL, T& vR,
-                                          T& ha, bool& bad) {
-  T riL, pL, cL, riR, pR, cR;
-  bad |= eos(ph, UL[0], UL[1], UL[2], UL[3], UL[4], UL[5], riL, pL, cL);
-  bad |= eos(ph, UR[0], UR[1], UR[2], UR[3], UR[4], UR[5], riR, pR, cR);
-  const T snL = d == 0 ? UL[1] : (d == 1 ? UL[2] : UL[3]);
-  const T snR = d == 0 ? UR[1] : (d == 1 ? UR[2] : UR[3]);
-  vL = snL * riL;
-  vR = snR * riR;
-  ha = T(0.5) * fmax(fabs(vL) + cL, fabs(vR) + cR);
-  T FL[NF_CORE], FR[NF_CORE];
-  FL[0] = snL;
-  FR[0] = snR;
+__device__ __forceinline__ void core_flux(const Phys<double>& ph, int d,
+                                          const double (&UL)[NF_CORE],
+                                          const double (&UR)[NF_CORE], double (&H)[NF_CORE],
+                                          double& vL, double& vR, double& ha, bool& bad) {
+  const EosPair<double> e = eos_pair(ph, UL, UR, bad);
+  const double snL = d == 0 ? UL[1] : (d == 1 ? UL[2] : UL[3]);
+  const double snR = d == 0 ? UR[1] : (d == 1 ? UR[2] : UR[3]);
+  vL = snL * e.riL;
+  vR = snR * e.riR;
+  ha = 0.5 * fmax(fabs(vL) + e.cL, fabs(vR) + e.cR);
+  H[0] = snL + snR;
 #pragma unroll
   for (int m = 0; m < 3; ++m) {
-    const T fl = UL[1 + m] * vL;
-    const T fr = UR[1 + m] * vR;
-    FL[1 + m] = m == d ? fl + pL : fl;
-    FR[1 + m] = m == d ? fr + pR : fr;
+    const double fl = UL[1 + m] * vL;
+    const double fr = UR[1 + m] * vR;
+    H[1 + m] = (m == d ? fl + e.pL : fl) + (m == d ? fr + e.pR : fr);
   }
-  FL[4] = (UL[4] + pL) * vL;
-  FR[4] = (UR[4] + pR) * vR;
-  FL[5] = UL[5] * vL;
-  FR[5] = UR[5] * vR;
+  H[4] = (UL[4] + e.pL) * vL + (UR[4] + e.pR) * vR;
+  H[5] = UL[5] * vL + UR[5] * vR;
 #pragma unroll
-  for (int f = 0; f < NF_CORE; ++f) H[f] = T(0.5) * (FL[f] + FR[f]) - ha * (UR[f] - UL[f]);
+  for (int f = 0; f < NF_CORE; ++f) H[f] = fma(0.5, H[f], -(ha * (UR[f] - UL[f])));
 }
 
 // binary32: the same flux with the products and sums of each field fused,
@@ -745,7 +839,7 @@ __device__ __forceinline__ void core_flux(const Phys<float>& ph, int d,
                                           const float (&UL)[NF_CORE],
                                           const float (&UR)[NF_CORE], float (&H)[NF_CORE],
                                           float& vL, float& vR, float& ha, bool& bad) {
-  const EosPair e = eos_pair(ph, UL, UR, bad);
+  const EosPair<float> e = eos_pair(ph, UL, UR, bad);
   const float snL = d == 0 ? UL[1] : (d == 1 ? UL[2] : UL[3]);
   const float snR = d == 0 ? UR[1] : (d == 1 ? UR[2] : UR[3]);
   vL = snL * e.riL;
@@ -765,13 +859,31 @@ __device__ __forceinline__ void core_flux(const Phys<float>& ph, int d,
   for (int f = 0; f < NF_CORE; ++f) H[f] = fmaf(-ha, UR[f] - UL[f], H[f]);
 }
 
+// Rotating-frame sources of s_x, s_y, s_z, E of a cell in column (x, y) of the
+// leaf from its Uk.  The lane's place goes through fresh() so that the
+// coordinates are worked out here and not kept through the stream loops of
+// every run, rotating or not.
+__device__ __forceinline__ int fresh(int v);
+__device__ __forceinline__ void rotating_source(const GridArgs& g, const LeafInfo& li, int x,
+                                                int y, double rho, double sx, double sy,
+                                                double (&src)[4]) {
+  const double dx = 1.0 / (double)(SUB * fresh(li.blocks));
+  const double rx = ((double)(SUB * li.ix + fresh(x)) + 0.5) * dx - 0.5;
+  const double ry = ((double)(SUB * li.iy + fresh(y)) + 0.5) * dx - 0.5;
+  const double om2 = g.omega * g.omega, tw = 2.0 * g.omega;
+  src[0] = tw * sy + rho * om2 * rx;
+  src[1] = rho * om2 * ry - tw * sx;
+  src[2] = 0.0;
+  src[3] = om2 * (sx * rx + sy * ry);
+}
+
 // Stage combination of one cell: t = Uk + dt L with L = -sum * inv_dx, then
 // t (first stage) or U0 + beta (t - U0); u0 is the cell's U0 value, loaded
 // by the caller ahead of time.
 template <typename T>
-__device__ __forceinline__ T finish_cell(const StepArgs& s, size_t fbase, uint32_t cell, T uk,
-                                         T u0, double sum, bool has_src, double src, double dt,
-                                         double inv_dx) {
+__device__ __forceinline__ T finish_cell(const StepArgs& s, const FieldView& out_f,
+                                         uint32_t cell, T uk, T u0, double sum, bool has_src,
+                                         double src, double dt, double inv_dx) {
   double lrate = -sum * inv_dx;
   if (has_src) lrate = lrate + src;
   const double t = (double)uk + dt * lrate;
@@ -783,7 +895,7 @@ __device__ __forceinline__ T finish_cell(const StepArgs& s, size_t fbase, uint32
     out = t;
   }
   // the result is not read again by this kernel: keep it out of the caches
-  __builtin_nontemporal_store((T)out, static_cast<T*>(s.Uout) + fbase + cell);
+  bstore_once((T)out, out_f, (uint32_t)sizeof(T) * cell);
   return (T)out;
 }
 
@@ -906,8 +1018,7 @@ __device__ __forceinline__ void stream_step(const Phys<T>& ph, int d, Ppm<T> (&s
 // whichever lane gets there first, with no branch on the lane.
 template <typename T, int NF, int AP>
 __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, const LeafInfo& li,
-                                         const FaceNbr& fn, double* __restrict__ acc, int h,
-                                         int lane, bool& bad) {
+                                         double* __restrict__ acc, int h, int lane, bool& bad) {
   const GridArgs& g = s.g;
   const size_t fs = (size_t)g.n_leaves * CELLS;
   const uint32_t fs_b = (uint32_t)(fs * sizeof(T));
@@ -916,7 +1027,7 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
   const int d = lane >> 5;
   const int a = lane & 7;
   const int zz = (lane >> 3) & 3;
-  const Pencil p = make_pencil<T>(g, li, d, a, 4 * h + zz, fn);
+  const Pencil p = make_pencil<T>(li, d, a, 4 * h + zz);
   using L = AccLayout<AP>;
   const int acc_off = d == 0 ? zz * L::PLANE + a * L::PITCH : zz * L::PLANE + a;
   const int acc_step = d == 0 ? 1 : L::PITCH;
@@ -942,7 +1053,8 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
     if (k + 1 < TW) load_position<T, NF>(S, pencil_src(p, k + 1), qnext);
     T H[NF];
     stream_step<T, NF>(ph, d, st, qn, H, bad);
-    if (g.reg && (k == 5 || k == TW - 1)) record_face<T, NF>(g, fn, k - 5, a, 4 * h + zz, H);
+    if (g.reg && (k == 5 || k == TW - 1)) 
+      record_faces<T, NF, 0, NF>(g, li.leaf, d, k - 5, a, 4 * h + zz, H);
     if (k >= 6) {
       const int i = k - 6;  // interior cell along d: H now is its high face
       const int ai = acc_off + i * acc_step;
@@ -968,8 +1080,7 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
 // two wavefronts per SIMD it was 1 % slower.
 template <typename T, int NF, int MODE, int ZU, int AP>
 __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, const LeafInfo& li,
-                                        const FaceNbr& fn, double* __restrict__ acc, int h,
-                                        int lane, double dt, double inv_dx, bool& bad,
+                                        double* __restrict__ acc, int h, int lane, double dt, double inv_dx, bool& bad,
                                         double& cflmin, int lnode) {
   const GridArgs& g = s.g;
   const size_t fs = (size_t)g.n_leaves * CELLS;
@@ -977,8 +1088,9 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
   const uint32_t rn_fs = (uint32_t)((size_t)g.n_nodes * CELLS * sizeof(T));
   const Sources S = make_sources(s.Uk, g.rstate, g.nf, fs_b, rn_fs);
   const Rsrc U0 = state_rsrc(s.U0 ? s.U0 : s.Uk, (uint32_t)(g.nf * fs * sizeof(T)));
+  const Rsrc UO = state_rsrc(s.Uout, (uint32_t)(g.nf * fs * sizeof(T)));
   const int x = lane & 7, y = lane >> 3;
-  const Pencil p = make_pencil<T>(g, li, 2, x, y, fn);
+  const Pencil p = make_pencil<T>(li, 2, x, y);
   const int k0 = 4 * h;
   const uint32_t leaf_at = (uint32_t)li.leaf * CELLS + y * 8 + x;
 
@@ -1011,7 +1123,8 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
     }
     T H[NF];
     stream_step<T, NF>(ph, 2, st, qn, H, bad);
-    if (g.reg && (k == 5 || k == TW - 1)) record_face<T, NF>(g, fn, k - 5, x, y, H);
+    if (g.reg && (k == 5 || k == TW - 1)) 
+      record_faces<T, NF, 0, NF>(g, li.leaf, 2, k - 5, x, y, H);
     if (kk >= 6) {
       const int i = k - 6;  // interior cell along z
       using L = AccLayout<AP>;
@@ -1020,20 +1133,13 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
       double src[4] = {0.0, 0.0, 0.0, 0.0};
       const bool rot = g.omega != 0.0;
       if (rot) {
-        const double dx = 1.0 / (double)(SUB * li.blocks);
-        const double rx = ((double)(SUB * li.ix + x) + 0.5) * dx - 0.5;
-        const double ry = ((double)(SUB * li.iy + y) + 0.5) * dx - 0.5;
-        const double rho = (double)st[0].qy, sx = (double)st[1].qy, sy = (double)st[2].qy;
-        const double om2 = g.omega * g.omega, tw = 2.0 * g.omega;
-        src[0] = tw * sy + rho * om2 * rx;
-        src[1] = rho * om2 * ry - tw * sx;
-        src[3] = om2 * (sx * rx + sy * ry);
+        rotating_source(g, li, x, y, (double)st[0].qy, (double)st[1].qy, (double)st[2].qy, src);
       }
       T cv[NF_CORE];
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
         const double sum = acc[f * L::HALF + ai] + ((double)H[f] - Hprev[f]);
-        const T o = finish_cell<T>(s, (size_t)f * fs, leaf_at + i * 64, st[f].qy, u0v[f], sum,
+        const T o = finish_cell<T>(s, FieldView{UO, f * fs_b}, leaf_at + i * 64, st[f].qy, u0v[f], sum,
                                    rot && f >= 1 && f <= 4, f >= 1 && f <= 4 ? src[f - 1] : 0.0,
                                    dt, inv_dx);
         if (f < NF_CORE) cv[f] = o;
@@ -1063,41 +1169,7 @@ __global__ void __launch_bounds__(64, W) k_step(StepArgs s) {
   if (leaf >= g.n_leaves) return;
   const int lane = threadIdx.x;
 
-  LeafInfo li;
-  li.leaf = leaf;
-  const int4 c4 = reinterpret_cast<const int4*>(g.coord)[leaf];
-  li.ix = c4.y;
-  li.iy = c4.z;
-  li.iz = c4.w;
-  li.blocks = g.base << c4.x;
-  // face-neighbour slots: -x 12, +x 14, -y 10, +y 16, -z 4, +z 22
-  const uint8_t* kd = g.kind + 27 * leaf;
-  const int32_t* nb = g.nbr + 27 * leaf;
-  const bool xlane = lane < 32;  // phase XY: lanes 0-31 x-pencils, 32-63 y-pencils
-  FaceNbr fxy, fz;
-  fxy.klo = xlane ? (int)kd[12] : (int)kd[10];
-  fxy.ilo = xlane ? nb[12] : nb[10];
-  fxy.khi = xlane ? (int)kd[14] : (int)kd[16];
-  fxy.ihi = xlane ? nb[14] : nb[16];
-  fz.klo = kd[4];
-  fz.ilo = nb[4];
-  fz.khi = kd[22];
-  fz.ihi = nb[22];
-  fxy.rlo = fxy.rhi = fxy.flo = fxy.fhi = -1;
-  fz.rlo = fz.rhi = fz.flo = fz.fhi = -1;
-  if (g.reg) {
-    // register slots per face orientation o = 2*axis + side
-    const int32_t* fsl = g.face_slot + 6 * leaf;
-    const int32_t* fin = g.fine_slot + 6 * leaf;
-    fxy.rlo = xlane ? fsl[0] : fsl[2];
-    fxy.rhi = xlane ? fsl[1] : fsl[3];
-    fxy.flo = xlane ? fin[0] : fin[2];
-    fxy.fhi = xlane ? fin[1] : fin[3];
-    fz.rlo = fsl[4];
-    fz.rhi = fsl[5];
-    fz.flo = fin[4];
-    fz.fhi = fin[5];
-  }
+  const LeafInfo li = leaf_info(g, leaf);
   const double dt = *s.dt;
   const double inv_dx = (double)(SUB * li.blocks);
   Phys<T> ph;
@@ -1110,10 +1182,10 @@ __global__ void __launch_bounds__(64, W) k_step(StepArgs s) {
   const int lnode = MODE == STEP_RESTRICT ? g.leaf_node[leaf] : -1;
 #pragma unroll 1
   for (int h = 0; h < 2; ++h) {
-    phase_xy<T, NF, AP>(s, ph, li, fxy, acc, h, lane, bad);
+    phase_xy<T, NF, AP>(s, ph, li, acc, h, fresh(lane), bad);
     wave_lds_sync();
-    phase_z<T, NF, MODE, W == 1 ? 2 : 1, AP>(s, ph, li, fz, acc, h, lane, dt, inv_dx, bad, cflmin,
-                                             lnode);
+    phase_z<T, NF, MODE, W == 1 ? 2 : 1, AP>(s, ph, li, acc, h, fresh(lane), dt, inv_dx, bad,
+                                             cflmin, lnode);
     wave_lds_sync();
   }
   if constexpr (MODE == STEP_CFL) atomic_min_positive(s.dt_next, cflmin, lane);
@@ -1148,6 +1220,7 @@ __device__ __forceinline__ void load_group(const Sources& S, const Src& s, T (&q
     if (s.ref) {
 #pragma unroll
       for (int i = 0; i < NG; ++i) q[i] = bload(T(), FieldView{S.rn, (F0 + i) * S.rn_fs}, s.o);
+      branches_apart();
     } else {
 #pragma unroll
       for (int i = 0; i < NG; ++i) q[i] = bload(T(), FieldView{S.uk, (F0 + i) * S.uk_fs}, s.o);
@@ -1172,27 +1245,6 @@ __device__ __forceinline__ void prologue_group(Ppm<T> (&st)[NG], const Sources& 
       ppm_push(st[f], cur[f], j, ul, ur);
       cur[f] = nxt[f];
     }
-  }
-}
-
-// Fluxes of fields [F0, F0 + NG) through face `face` of a pencil, recorded
-// for the coarse-fine correction (see record_face).
-template <typename T, int NF, int F0, int NG>
-__device__ __forceinline__ void record_group(const GridArgs& g, const FaceNbr& fn, int face,
-                                             int u, int v, const T (&H)[NG]) {
-  const int cs = face == 0 ? fn.rlo : fn.rhi;
-  const int fe = face == 0 ? fn.flo : fn.fhi;
-  if (cs >= 0) {
-    double* r = g.reg + (size_t)cs * NF * REG_STRIDE + u + 8 * v;
-#pragma unroll
-    for (int f = 0; f < NG; ++f) r[(F0 + f) * REG_STRIDE] = (double)H[f];
-  }
-  if (fe >= 0) {
-    const int q = fe & 3;
-    double* r = g.reg + (size_t)(fe >> 2) * NF * REG_STRIDE + REG_COARSE +
-                (8 * (q & 1) + u) + 16 * (8 * (q >> 1) + v);
-#pragma unroll
-    for (int f = 0; f < NG; ++f) r[(F0 + f) * REG_STRIDE] = (double)H[f];
   }
 }
 
@@ -1236,7 +1288,7 @@ __device__ __forceinline__ void group_step(const Phys<T>& ph, int d, Ppm<T> (&st
 // Phase XY of half h for one field group (see phase_xy).
 template <typename T, int NF, int F0, int NG>
 __device__ __forceinline__ void phase_xy_group(const StepArgs& s, const Phys<T>& ph,
-                                               const LeafInfo& li, const FaceNbr& fn,
+                                               const LeafInfo& li,
                                                double* __restrict__ acc,
                                                SpeedSlot<T>* __restrict__ spd, int& sn, int h,
                                                int lane, bool& bad) {
@@ -1248,7 +1300,7 @@ __device__ __forceinline__ void phase_xy_group(const StepArgs& s, const Phys<T>&
   const int d = lane >> 5;
   const int a = lane & 7;
   const int zz = (lane >> 3) & 3;
-  const Pencil p = make_pencil<T>(g, li, d, a, 4 * h + zz, fn);
+  const Pencil p = make_pencil<T>(li, d, a, 4 * h + zz);
   const int acc_off = d == 0 ? zz * ACC_PLANE + a * ACC_PITCH : zz * ACC_PLANE + a;
   const int acc_step = d == 0 ? 1 : ACC_PITCH;
 
@@ -1275,7 +1327,7 @@ __device__ __forceinline__ void phase_xy_group(const StepArgs& s, const Phys<T>&
     group_step<T, F0, NG>(ph, d, st, qn, H, spd, sn & 1, lane, bad);
     ++sn;
     if (g.reg && (k == 5 || k == TW - 1))
-      record_group<T, NF, F0, NG>(g, fn, k - 5, a, 4 * h + zz, H);
+      record_faces<T, NF, F0, NG>(g, li.leaf, d, k - 5, a, 4 * h + zz, H);
     if (k >= 6) {
       const int ai = acc_off + (k - 6) * acc_step;
       double dH[NG];
@@ -1295,7 +1347,7 @@ __device__ __forceinline__ void phase_xy_group(const StepArgs& s, const Phys<T>&
 // the rotating-frame sources.
 template <typename T, int NF, int F0, int NG, int MODE>
 __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& ph,
-                                              const LeafInfo& li, const FaceNbr& fn,
+                                              const LeafInfo& li,
                                               double* __restrict__ acc,
                                               SpeedSlot<T>* __restrict__ spd, int& sn, int h,
                                               int lane, double dt, double inv_dx, bool& bad,
@@ -1306,8 +1358,9 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
   const uint32_t rn_fs = (uint32_t)((size_t)g.n_nodes * CELLS * sizeof(T));
   const Sources S = make_sources(s.Uk, g.rstate, g.nf, fs_b, rn_fs);
   const Rsrc U0 = state_rsrc(s.U0 ? s.U0 : s.Uk, (uint32_t)(g.nf * fs * sizeof(T)));
+  const Rsrc UO = state_rsrc(s.Uout, (uint32_t)(g.nf * fs * sizeof(T)));
   const int x = lane & 7, y = lane >> 3;
-  const Pencil p = make_pencil<T>(g, li, 2, x, y, fn);
+  const Pencil p = make_pencil<T>(li, 2, x, y);
   const int k0 = 4 * h;
   const uint32_t leaf_at = (uint32_t)li.leaf * CELLS + y * 8 + x;
 
@@ -1340,28 +1393,22 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
     T H[NG];
     group_step<T, F0, NG>(ph, 2, st, qn, H, spd, sn & 1, lane, bad);
     ++sn;
-    if (g.reg && (k == 5 || k == TW - 1)) record_group<T, NF, F0, NG>(g, fn, k - 5, x, y, H);
+    if (g.reg && (k == 5 || k == TW - 1)) 
+      record_faces<T, NF, F0, NG>(g, li.leaf, 2, k - 5, x, y, H);
     if (kk >= 6) {
       const int i = k - 6;  // interior cell along z
       const int ai = (i - k0) * ACC_PLANE + y * ACC_PITCH + x;
       double src[4] = {0.0, 0.0, 0.0, 0.0};
       const bool rot = F0 == 0 && g.omega != 0.0;
       if (rot) {
-        const double dx = 1.0 / (double)(SUB * li.blocks);
-        const double rx = ((double)(SUB * li.ix + x) + 0.5) * dx - 0.5;
-        const double ry = ((double)(SUB * li.iy + y) + 0.5) * dx - 0.5;
-        const double rho = (double)st[0].qy, sx = (double)st[1].qy, sy = (double)st[2].qy;
-        const double om2 = g.omega * g.omega, tw = 2.0 * g.omega;
-        src[0] = tw * sy + rho * om2 * rx;
-        src[1] = rho * om2 * ry - tw * sx;
-        src[3] = om2 * (sx * rx + sy * ry);
+        rotating_source(g, li, x, y, (double)st[0].qy, (double)st[1].qy, (double)st[2].qy, src);
       }
       T cv[NF_CORE];
 #pragma unroll
       for (int f = 0; f < NG; ++f) {
         const int fg = F0 + f;
         const double sum = acc[fg * ACC_HALF + ai] + ((double)H[f] - Hprev[f]);
-        const T o = finish_cell<T>(s, (size_t)fg * fs, leaf_at + i * 64, st[f].qy, u0v[f], sum,
+        const T o = finish_cell<T>(s, FieldView{UO, fg * fs_b}, leaf_at + i * 64, st[f].qy, u0v[f], sum,
                                    rot && fg >= 1 && fg <= 4,
                                    fg >= 1 && fg <= 4 ? src[fg - 1] : 0.0, dt, inv_dx);
         if (F0 == 0 && f < NF_CORE) cv[f] = o;
@@ -1394,39 +1441,7 @@ __global__ void __launch_bounds__(128, W) k_step2(StepArgs s) {
   const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) ^ (blockIdx.x & 1));
   const int lane = threadIdx.x & 63;
 
-  LeafInfo li;
-  li.leaf = leaf;
-  const int4 c4 = reinterpret_cast<const int4*>(g.coord)[leaf];
-  li.ix = c4.y;
-  li.iy = c4.z;
-  li.iz = c4.w;
-  li.blocks = g.base << c4.x;
-  const uint8_t* kd = g.kind + 27 * leaf;
-  const int32_t* nb = g.nbr + 27 * leaf;
-  const bool xlane = lane < 32;
-  FaceNbr fxy, fz;
-  fxy.klo = xlane ? (int)kd[12] : (int)kd[10];
-  fxy.ilo = xlane ? nb[12] : nb[10];
-  fxy.khi = xlane ? (int)kd[14] : (int)kd[16];
-  fxy.ihi = xlane ? nb[14] : nb[16];
-  fz.klo = kd[4];
-  fz.ilo = nb[4];
-  fz.khi = kd[22];
-  fz.ihi = nb[22];
-  fxy.rlo = fxy.rhi = fxy.flo = fxy.fhi = -1;
-  fz.rlo = fz.rhi = fz.flo = fz.fhi = -1;
-  if (g.reg) {
-    const int32_t* fsl = g.face_slot + 6 * leaf;
-    const int32_t* fin = g.fine_slot + 6 * leaf;
-    fxy.rlo = xlane ? fsl[0] : fsl[2];
-    fxy.rhi = xlane ? fsl[1] : fsl[3];
-    fxy.flo = xlane ? fin[0] : fin[2];
-    fxy.fhi = xlane ? fin[1] : fin[3];
-    fz.rlo = fsl[4];
-    fz.rhi = fsl[5];
-    fz.flo = fin[4];
-    fz.fhi = fin[5];
-  }
+  const LeafInfo li = leaf_info(g, leaf);
   const double dt = *s.dt;
   const double inv_dx = (double)(SUB * li.blocks);
   Phys<T> ph;
@@ -1442,15 +1457,15 @@ __global__ void __launch_bounds__(128, W) k_step2(StepArgs s) {
 #pragma unroll 1
   for (int h = 0; h < 2; ++h) {
     if (wave == 0)
-      phase_xy_group<T, NF, 0, NF_CORE>(s, ph, li, fxy, acc, spd, sn, h, lane, bad);
+      phase_xy_group<T, NF, 0, NF_CORE>(s, ph, li, acc, spd, sn, h, fresh(lane), bad);
     else
-      phase_xy_group<T, NF, NF_CORE, NS>(s, ph, li, fxy, acc, spd, sn, h, lane, bad);
+      phase_xy_group<T, NF, NF_CORE, NS>(s, ph, li, acc, spd, sn, h, fresh(lane), bad);
     wave_lds_sync();
     if (wave == 0)
-      phase_z_group<T, NF, 0, NF_CORE, MODE>(s, ph, li, fz, acc, spd, sn, h, lane, dt, inv_dx,
+      phase_z_group<T, NF, 0, NF_CORE, MODE>(s, ph, li, acc, spd, sn, h, fresh(lane), dt, inv_dx,
                                             bad, cflmin, lnode);
     else
-      phase_z_group<T, NF, NF_CORE, NS, MODE>(s, ph, li, fz, acc, spd, sn, h, lane, dt, inv_dx,
+      phase_z_group<T, NF, NF_CORE, NS, MODE>(s, ph, li, acc, spd, sn, h, fresh(lane), dt, inv_dx,
                                              bad, cflmin, lnode);
     wave_lds_sync();
   }

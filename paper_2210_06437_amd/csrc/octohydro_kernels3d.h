@@ -35,14 +35,14 @@ namespace octohydro {
 // limited slopes change sign exactly (or stay +0), the interface values and
 // the monotonisation are symmetric in the two ends, and every sum involved
 // is commutative.
-template <typename T>
-__device__ __forceinline__ void parabola(const T* __restrict__ t, int s, T& l, T& r) {
-  const T q0 = t[-2 * s], q1 = t[-s], q2 = t[0], q3 = t[s], q4 = t[2 * s];
-  const T dm1 = limited_slope(q0, q1, q2);
-  const T dm2 = limited_slope(q1, q2, q3);
-  const T dm3 = limited_slope(q2, q3, q4);
-  l = T(0.5) * (q1 + q2) - (dm2 - dm1) * T(1.0 / 6.0);
-  r = T(0.5) * (q2 + q3) - (dm3 - dm2) * T(1.0 / 6.0);
+__device__ __forceinline__ void parabola(const double* __restrict__ t, int s, double& l,
+                                         double& r) {
+  const double q0 = t[-2 * s], q1 = t[-s], q2 = t[0], q3 = t[s], q4 = t[2 * s];
+  const double h1 = half_slope(q0, q1, q2);
+  const double h2 = half_slope(q1, q2, q3);
+  const double h3 = half_slope(q2, q3, q4);
+  l = interface_value(q1, q2, h1, h2);
+  r = interface_value(q2, q3, h2, h3);
   monotonise(q2, l, r);
 }
 
@@ -90,13 +90,28 @@ __device__ __forceinline__ constexpr PointLine face_point(int sd, int pu, int pv
                                                    : point_line(pu, pv, sd));
 }
 
+// The Simpson sum ((corners + 4 edges) + 16 centre) / 36.  The products by 4
+// and 16 are exact, so each FMA rounds once, as the addition does; the
+// division is by the reciprocal with Markstein's residual correction, which
+// gives the correctly rounded quotient in 3 instructions.
+__device__ __forceinline__ double simpson_close(double corners, double edges, double centre) {
+  const double x = fma(16.0, centre, fma(4.0, edges, corners));
+  const double q = x * (1.0 / 36.0);
+  return fma(fma(-36.0, q, x), 1.0 / 36.0, q);
+}
+__device__ __forceinline__ float simpson_close(float corners, float edges, float centre) {
+  const float x = fmaf(16.0f, centre, fmaf(4.0f, edges, corners));
+  const float q = x * (1.0f / 36.0f);
+  return fmaf(fmaf(-36.0f, q, x), 1.0f / 36.0f, q);
+}
+
 // Simpson combination of the 9 point values of one field, points in the
 // order (-1,-1), (1,1), (1,-1), (-1,1), (0,-1), (0,1), (-1,0), (1,0), (0,0).
 template <typename T>
 __device__ __forceinline__ T simpson9(const T (&h)[9]) {
   const T corners = (h[0] + h[1]) + (h[2] + h[3]);
   const T edges = (h[4] + h[5]) + (h[6] + h[7]);
-  return ((corners + T(4) * edges) + T(16) * h[8]) / T(36);
+  return simpson_close(corners, edges, h[8]);
 }
 
 // Flux of all fields through the face between tile cells tl and tl + stride
@@ -150,20 +165,6 @@ __device__ __forceinline__ void face_flux_3d(const Phys<T>& ph, const T* __restr
   }
 }
 
-// Face-neighbour register slots of the faces normal to axis D.
-__device__ __forceinline__ FaceNbr face_slots_3d(const GridArgs& g, int leaf, int D) {
-  FaceNbr fn;
-  fn.klo = fn.ilo = fn.khi = fn.ihi = 0;
-  fn.rlo = fn.rhi = fn.flo = fn.fhi = -1;
-  if (g.reg) {
-    fn.rlo = g.face_slot[6 * leaf + 2 * D];
-    fn.rhi = g.face_slot[6 * leaf + 2 * D + 1];
-    fn.flo = g.fine_slot[6 * leaf + 2 * D];
-    fn.fhi = g.fine_slot[6 * leaf + 2 * D + 1];
-  }
-  return fn;
-}
-
 // Tile index of leaf cell (x, y, z); -1 and 8 name the ghost layers.
 __device__ __forceinline__ constexpr int tile_at(int x, int y, int z) {
   return (x + GH) + (y + GH) * TW + (z + GH) * TW * TW;
@@ -195,13 +196,7 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
   const int leaf = s.leaf_base + blockIdx.x;
   if (leaf >= g.n_leaves) return;
   const int lane = threadIdx.x;
-  LeafInfo li;
-  li.leaf = leaf;
-  const int4 c4 = reinterpret_cast<const int4*>(g.coord)[leaf];
-  li.ix = c4.y;
-  li.iy = c4.z;
-  li.iz = c4.w;
-  li.blocks = g.base << c4.x;
+  const LeafInfo li = leaf_info(g, leaf);
   const double dt = *s.dt;
   const double inv_dx = (double)(SUB * li.blocks);
   Phys<T> ph;
@@ -210,10 +205,9 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
   ph.eta1 = (T)g.eta1;
   const size_t fsG = (size_t)g.n_leaves * TILE;
   const size_t fs = (size_t)g.n_leaves * CELLS;
+  const uint32_t fs_b = (uint32_t)(fs * sizeof(T));
+  const Rsrc UO = state_rsrc(s.Uout, (uint32_t)(g.nf * fs * sizeof(T)));
   const T* __restrict__ Gt = G + (size_t)leaf * TILE;
-  const FaceNbr fx = face_slots_3d(g, leaf, 0);
-  const FaceNbr fy = face_slots_3d(g, leaf, 1);
-  const FaceNbr fz = face_slots_3d(g, leaf, 2);
   const int x = lane & 7, y = lane >> 3;
   bool bad = false;
   const double dx = 1.0 / (double)(SUB * li.blocks);
@@ -240,12 +234,12 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
       face_flux_3d<T, NF, 0>(ph, Gt, fsG, first ? tile_at(SUB - 1, x, y) : tile_at(x - 1, y, z),
                              H, bad);
       if (first) {
-        if (g.reg) record_face<T, NF>(g, fx, SUB, x, y, H);
+        if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 0, SUB, x, y, H);
 #pragma unroll
         for (int f = 0; f < NF; ++f) hx8[f * 64 + lane] = (double)H[f];
         continue;
       }
-      if (g.reg && x == 0) record_face<T, NF>(g, fx, 0, y, z, H);
+      if (g.reg && x == 0) record_faces<T, NF, 0, NF>(g, leaf, 0, 0, y, z, H);
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
         const double lo = (double)H[f];
@@ -263,12 +257,12 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
       face_flux_3d<T, NF, 1>(ph, Gt, fsG, first ? tile_at(x, SUB - 1, y) : tile_at(x, y - 1, z),
                              H, bad);
       if (first) {
-        if (g.reg) record_face<T, NF>(g, fy, SUB, x, y, H);
+        if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 1, SUB, x, y, H);
 #pragma unroll
         for (int f = 0; f < NF; ++f) hy8[f * 64 + lane] = (double)H[f];
         continue;
       }
-      if (g.reg && y == 0) record_face<T, NF>(g, fy, 0, x, z, H);
+      if (g.reg && y == 0) record_faces<T, NF, 0, NF>(g, leaf, 1, 0, x, z, H);
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
         const double lo = (double)H[f];
@@ -283,12 +277,12 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
       T H[NF];
       face_flux_3d<T, NF, 2>(ph, Gt, fsG, tile_at(x, y, z), H, bad);
       if (zl < 0) {
-        if (g.reg) record_face<T, NF>(g, fz, 0, x, y, H);
+        if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 2, 0, x, y, H);
 #pragma unroll
         for (int f = 0; f < NF; ++f) hz3[f * 64 + lane] = (double)H[f];
         continue;
       }
-      if (g.reg && z == SUB - 1) record_face<T, NF>(g, fz, SUB, x, y, H);
+      if (g.reg && z == SUB - 1) record_faces<T, NF, 0, NF>(g, leaf, 2, SUB, x, y, H);
       const T* __restrict__ ukc = Gt + tile_at(x, y, z);  // the cell's Uk
       double src[4] = {0.0, 0.0, 0.0, 0.0};
       const bool rot = g.omega != 0.0;
@@ -305,7 +299,7 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
         const double sum = acc3[f * 256 + zl * 64 + lane] + ((double)H[f] - hz3[f * 64 + lane]);
         hz3[f * 64 + lane] = (double)H[f];
         const T u0 = s.U0 ? static_cast<const T*>(s.U0)[(size_t)f * fs + at] : T(0);
-        finish_cell<T>(s, (size_t)f * fs, at, ukc[f * fsG], u0, sum, rot && f >= 1 && f <= 4,
+        finish_cell<T>(s, FieldView{UO, f * fs_b}, at, ukc[f * fsG], u0, sum, rot && f >= 1 && f <= 4,
                        f >= 1 && f <= 4 ? src[f - 1] : 0.0, dt, inv_dx);
       }
     }
@@ -328,11 +322,11 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
     face_flux_3d<T, NF, 0>(ph, Gt, fsG, first ? tile_at(SUB - 1, x, y) : tile_at(x - 1, y, z),
                            H, bad);
     if (first) {
-      if (g.reg) record_face<T, NF>(g, fx, SUB, x, y, H);
+      if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 0, SUB, x, y, H);
 #pragma unroll
       for (int f = 0; f < NF; ++f) hx8[f * 64 + lane] = (double)H[f];
     } else {
-      if (g.reg && x == 0) record_face<T, NF>(g, fx, 0, y, z, H);
+      if (g.reg && x == 0) record_faces<T, NF, 0, NF>(g, leaf, 0, 0, y, z, H);
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
         const double lo = (double)H[f];
@@ -344,11 +338,11 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
     face_flux_3d<T, NF, 1>(ph, Gt, fsG, first ? tile_at(x, SUB - 1, y) : tile_at(x, y - 1, z),
                            H, bad);
     if (first) {
-      if (g.reg) record_face<T, NF>(g, fy, SUB, x, y, H);
+      if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 1, SUB, x, y, H);
 #pragma unroll
       for (int f = 0; f < NF; ++f) hy8[f * 64 + lane] = (double)H[f];
     } else {
-      if (g.reg && y == 0) record_face<T, NF>(g, fy, 0, x, z, H);
+      if (g.reg && y == 0) record_faces<T, NF, 0, NF>(g, leaf, 1, 0, x, z, H);
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
         const double lo = (double)H[f];
@@ -359,12 +353,12 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
     }
     face_flux_3d<T, NF, 2>(ph, Gt, fsG, tile_at(x, y, z), H, bad);
     if (first) {
-      if (g.reg) record_face<T, NF>(g, fz, 0, x, y, H);
+      if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 2, 0, x, y, H);
 #pragma unroll
       for (int f = 0; f < NF; ++f) Hz[f] = (double)H[f];
       continue;
     }
-    if (g.reg && z == SUB - 1) record_face<T, NF>(g, fz, SUB, x, y, H);
+    if (g.reg && z == SUB - 1) record_faces<T, NF, 0, NF>(g, leaf, 2, SUB, x, y, H);
     const T* __restrict__ ukc = Gt + tile_at(x, y, z);  // the cell's Uk
     double src[4] = {0.0, 0.0, 0.0, 0.0};
     const bool rot = g.omega != 0.0;
@@ -381,7 +375,7 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
       const double sum = sxy[f] + ((double)H[f] - Hz[f]);
       Hz[f] = (double)H[f];
       const T u0 = s.U0 ? static_cast<const T*>(s.U0)[(size_t)f * fs + at] : T(0);
-      finish_cell<T>(s, (size_t)f * fs, at, ukc[f * fsG], u0, sum, rot && f >= 1 && f <= 4,
+      finish_cell<T>(s, FieldView{UO, f * fs_b}, at, ukc[f * fsG], u0, sum, rot && f >= 1 && f <= 4,
                      f >= 1 && f <= 4 ? src[f - 1] : 0.0, dt, inv_dx);
     }
   }
@@ -441,6 +435,8 @@ __device__ __forceinline__ void finish_leaf_3d(const StepArgs& s, const T (&Hs)[
   const double inv_dx = (double)(SUB * blocks);
   const double dx = 1.0 / (double)(SUB * blocks);
   const size_t fs = (size_t)g.n_leaves * CELLS;
+  const uint32_t fs_b = (uint32_t)(fs * sizeof(T));
+  const Rsrc UO = state_rsrc(s.Uout, (uint32_t)(g.nf * fs * sizeof(T)));
   const T* __restrict__ Uk = static_cast<const T*>(s.Uk);
   const T* __restrict__ U0 = static_cast<const T*>(s.U0);
 #pragma unroll 1
@@ -469,7 +465,7 @@ __device__ __forceinline__ void finish_leaf_3d(const StepArgs& s, const T (&Hs)[
       const double zhi = (double)Hs[18 + z + 1][f][xy];
       const double sum = ((xhi - xlo) + (yhi - ylo)) + (zhi - zlo);
       const T u0 = U0 ? U0[(size_t)f * fs + at] : T(0);
-      finish_cell<T>(s, (size_t)f * fs, at, Uk[(size_t)f * fs + at], u0, sum,
+      finish_cell<T>(s, FieldView{UO, f * fs_b}, at, Uk[(size_t)f * fs + at], u0, sum,
                      rot && f >= 1 && f <= 4, f >= 1 && f <= 4 ? src[f - 1] : 0.0, dt, inv_dx);
     }
   }
@@ -505,9 +501,8 @@ __global__ void __launch_bounds__(256, 1) k_step3d_wg(StepArgs s, const T* __res
       face_flux_3d<T, NF, 0>(ph, Gt, fsG, hi ? tile_at(SUB - 1, a, b) : tile_at(a - 1, b, fp.p),
                              H, bad);
       if (g.reg) {
-        const FaceNbr fn = face_slots_3d(g, leaf, 0);
-        if (hi) record_face<T, NF>(g, fn, SUB, a, b, H);
-        else if (a == 0) record_face<T, NF>(g, fn, 0, b, fp.p, H);
+        if (hi) record_faces<T, NF, 0, NF>(g, leaf, 0, SUB, a, b, H);
+        else if (a == 0) record_faces<T, NF, 0, NF>(g, leaf, 0, 0, b, fp.p, H);
       }
       slot = hi ? SUB : fp.p;
     } else if (fp.d == 1) {
@@ -515,15 +510,14 @@ __global__ void __launch_bounds__(256, 1) k_step3d_wg(StepArgs s, const T* __res
       face_flux_3d<T, NF, 1>(ph, Gt, fsG, hi ? tile_at(a, SUB - 1, b) : tile_at(a, b - 1, fp.p),
                              H, bad);
       if (g.reg) {
-        const FaceNbr fn = face_slots_3d(g, leaf, 1);
-        if (hi) record_face<T, NF>(g, fn, SUB, a, b, H);
-        else if (b == 0) record_face<T, NF>(g, fn, 0, a, fp.p, H);
+        if (hi) record_faces<T, NF, 0, NF>(g, leaf, 1, SUB, a, b, H);
+        else if (b == 0) record_faces<T, NF, 0, NF>(g, leaf, 1, 0, a, fp.p, H);
       }
       slot = 9 + (hi ? SUB : fp.p);
     } else {
       face_flux_3d<T, NF, 2>(ph, Gt, fsG, tile_at(a, b, fp.p - 1), H, bad);
       if (g.reg && (fp.p == 0 || fp.p == SUB))
-        record_face<T, NF>(g, face_slots_3d(g, leaf, 2), fp.p, a, b, H);
+        record_faces<T, NF, 0, NF>(g, leaf, 2, fp.p, a, b, H);
       slot = 18 + fp.p;
     }
 #pragma unroll
@@ -590,7 +584,7 @@ __device__ __forceinline__ void simpson_pair(int p, T hp, T hm, T& sa, T& sb, T&
   else if (p == 1) sa = sa + (hp + hm);
   else if (p == 2) sb = hm + hp;
   else if (p == 3) sb = sb + (hm + hp);
-  else out = ((sa + T(4) * sb) + T(16) * hp) / T(36);
+  else out = simpson_close(sa, sb, hp);
 }
 
 // Value of the previous cell along D within the lane's cell plane, lane
@@ -808,8 +802,8 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
       core_flux(ph, 1, YL, YR, hy, vly, vry, hay, by);
 #pragma unroll
       for (int f = 0; f < NF_CORE; ++f) {
-        Hx[f] = ((acc[f].xc + T(4) * acc[f].xe) + T(16) * hx[f]) / T(36);
-        Hy[f] = ((acc[f].yc + T(4) * acc[f].ye) + T(16) * hy[f]) / T(36);
+        Hx[f] = simpson_close(acc[f].xc, acc[f].xe, hx[f]);
+        Hy[f] = simpson_close(acc[f].yc, acc[f].ye, hy[f]);
         keep_order(Hx[f]);
         keep_order(Hy[f]);
       }
@@ -824,8 +818,8 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
       parabola(q, SY, ly, hye);
       const T cx = passive_flux(prev_cell<0>(hxe), lx, vlx, vrx, hax);
       const T cy = passive_flux(prev_cell<1>(hye), ly, vly, vry, hay);
-      Hx[f] = ((acc[f].xc + T(4) * acc[f].xe) + T(16) * cx) / T(36);
-      Hy[f] = ((acc[f].yc + T(4) * acc[f].ye) + T(16) * cy) / T(36);
+      Hx[f] = simpson_close(acc[f].xc, acc[f].xe, cx);
+      Hy[f] = simpson_close(acc[f].yc, acc[f].ye, cy);
       keep_order(Hx[f]);
       keep_order(Hy[f]);
     }
@@ -850,7 +844,7 @@ __device__ __forceinline__ void ws_boundary(const GridArgs& g, const Phys<T>& ph
   T H[NF];
   if (k < 2) {
     face_flux_3d<T, NF, 0>(ph, Gt, fsG, hi ? tile_at(SUB - 1, a, b) : tile_at(-1, a, b), H, bad);
-    if (g.reg) record_face<T, NF>(g, face_slots_3d(g, leaf, 0), hi ? SUB : 0, a, b, H);
+    if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 0, hi ? SUB : 0, a, b, H);
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
       if (hi) Hs[SUB][f][lane] = H[f];
@@ -858,7 +852,7 @@ __device__ __forceinline__ void ws_boundary(const GridArgs& g, const Phys<T>& ph
     }
   } else {
     face_flux_3d<T, NF, 1>(ph, Gt, fsG, hi ? tile_at(a, SUB - 1, b) : tile_at(a, -1, b), H, bad);
-    if (g.reg) record_face<T, NF>(g, face_slots_3d(g, leaf, 1), hi ? SUB : 0, a, b, H);
+    if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 1, hi ? SUB : 0, a, b, H);
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
       if (hi) Hs[9 + SUB][f][lane] = H[f];
@@ -975,7 +969,7 @@ __device__ __forceinline__ void ws_column(const GridArgs& g, const Phys<T>& ph,
 #pragma unroll
     for (int f = 0; f < NF; ++f) Hs[18 + c][f][lane] = H[f];
     if (g.reg && (c == 0 || c == SUB))
-      record_face<T, NF>(g, face_slots_3d(g, leaf, 2), c, x, y, H);
+      record_faces<T, NF, 0, NF>(g, leaf, 2, c, x, y, H);
   }
 }
 

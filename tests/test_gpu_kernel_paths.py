@@ -1,5 +1,5 @@
 """Paths of the kernels that the parity suites do not reach by their inputs:
-states far from one in binary32 (the range test of the face states)."""
+states far from one in binary32 and binary64 (the range test of the face states)."""
 import numpy as np
 import pytest
 
@@ -56,3 +56,61 @@ def test_fp32_states_far_from_one(env, rho_exp, p_exp, recon):
         err = np.abs(got[f] - ref[f]).max() / scale[f]
         print(f"  field {f}: {err:.2e}")
         assert err <= 2e-6, (f, err)
+
+
+@pytest.mark.parametrize("recon", [0, 1])
+@pytest.mark.parametrize("rho_exp,p_exp", [(0, 0), (-510, -510), (0, 510), (0, -510), (495, 10),
+                                           (-498, 0)])
+def test_fp64_states_far_from_one(env, rho_exp, p_exp, recon):
+    """The same in binary64, whose refined reciprocal and root are correctly
+    rounded inside the range they serve and IEEE outside it: the oracle's
+    bits."""
+    torch, hb = env
+    print(f"case rho 2^{rho_exp} p 2^{p_exp} recon {recon}", flush=True)
+    base, rng = 2, np.random.default_rng(8)
+    coord = inputs.uniform_leaves(base)
+    X, Y, Z = inputs.cell_centres(coord, base)
+    wave = 0.1 * np.sin(2 * np.pi * X) * np.cos(2 * np.pi * Y)
+    rho = 2.0 ** rho_exp * (1.0 + wave + 1e-2 * rng.uniform(-1, 1, X.shape))
+    p = 2.0 ** p_exp * (1.0 + 0.1 * np.cos(2 * np.pi * Z) + 1e-2 * rng.uniform(-1, 1, X.shape))
+    zero = np.zeros_like(rho)
+    U = inputs.conserved(rho, zero, zero, zero, p)
+    grid = hb.Grid(coord, base, 6, hb.HYDRO_F64, reconstruction=recon)
+    T = oracle.Table(coord, base)
+    dt_o = oracle.cfl_dt(T, U, 0.4)
+    dt = torch.tensor([dt_o], dtype=torch.float64, device="cuda")
+    out = grid.empty_state()
+    hb.hydro_step(grid, None, torch.from_numpy(U).to("cuda"), out, dt, 1.0)
+    oracle.set_recon(recon)
+    try:
+        ref, bad = oracle.step(T, U, dt_o)
+    finally:
+        oracle.set_recon(0)
+    assert bad == 0 and hb.hydro_check_status(grid) == hb.HYDRO_OK
+    assert np.array_equal(out.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("what", ["rho<0", "rho=0", "p<0", "nan"])
+def test_unphysical_states_are_reported(env, what, dtype):
+    """A state that meets rho <= 0, p <= 0 or NaN at a face sets the status,
+    from whichever field holds it."""
+    torch, hb = env
+    coord = inputs.uniform_leaves(2)
+    w = inputs.uniform_state(2)
+    U = w.U.copy()
+    if what == "rho<0":
+        U[0, 3] *= -1.0
+    elif what == "rho=0":
+        U[0, 3] = 0.0
+    elif what == "p<0":
+        U[4, 3] = -1.0
+        U[5, 3] = -1.0
+    else:
+        U[2, 3, 4, 4, 4] = np.nan
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    grid = hb.Grid(coord, 2, 6, dtype)
+    dt = torch.tensor([1e-4], dtype=torch.float64, device="cuda")
+    out = grid.empty_state()
+    hb.hydro_step(grid, None, torch.from_numpy(U).to("cuda").to(tdt).contiguous(), out, dt, 1.0)
+    assert hb.hydro_check_status(grid) == hb.HYDRO_E_UNPHYSICAL
