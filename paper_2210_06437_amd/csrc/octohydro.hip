@@ -499,11 +499,35 @@ static bool cfl_in_kernel(const hydro_grid* gr, const StepArgs& a) {
          get_options(gr->dtype, gr->n_fields).cfl_epilogue != 0;
 }
 
+// Batch size up to which each leaf gets a workgroup of its own (k_leaf) and
+// the launch shape of the options does not apply.  A k_leaf substep takes one
+// leaf's latency per 256 leaves (a CU works on one at a time), k_step and
+// k_step2 take theirs once up to 1024 wavefronts.  Later-stage substep, us,
+// k_leaf against the shape of default_options:
+//   binary64, fields    64 leaves      512          869
+//              6         14.2  39.2   30.3  45.2   61.5  53.2
+//              8         17.5  47.3   37.1  53.1   76.0  63.8
+//             11         22.8  41.5   49.1  56.3   98.4  70.9
+//             13         29.8  41.7   66.5  63.1  128.1  80.2
+//             16         49.2  66.3  136.7  97.7
+//   binary32   6          9.8  27.3   18.2  32.9   39.0  40.0
+//             11         14.9  31.8   29.7  36.6   60.4  47.4
+//             16         20.2  36.6   40.9  44.1   82.8  59.8
+static int whole_leaf_limit(int dtype, int nf) {
+  if (dtype == HYDRO_F64) return nf <= 9 ? 768 : (nf <= 12 ? 512 : 256);
+  return nf <= 10 ? 768 : 512;
+}
+
 static hipError_t launch_step(StepArgs a, int dtype, int blocks, hipStream_t st) {
   const Options o = get_options(dtype, a.g.nf);
   if (a.remap) a.remap = o.xcd_remap;
   const StepShape sh{o.waves_per_simd, o.waves_per_leaf};
   if (a.dt_next && a.node_out) return hipErrorInvalidValue;  // no kernel does both
+  if (blocks <= whole_leaf_limit(dtype, a.g.nf)) {
+    const int mode = a.dt_next ? STEP_CFL : (a.node_out ? STEP_RESTRICT : STEP_PLAIN);
+    return dtype == HYDRO_F64 ? launch_leaf_f64(a, mode, blocks, st)
+                              : launch_leaf_f32(a, mode, blocks, st);
+  }
   if (a.dt_next)
     return dtype == HYDRO_F64 ? launch_step_f64_cfl(a, blocks, sh, st)
                               : launch_step_f32_cfl(a, blocks, sh, st);

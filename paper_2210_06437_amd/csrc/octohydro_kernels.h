@@ -1475,6 +1475,158 @@ __global__ void __launch_bounds__(128, W) k_step2(StepArgs s) {
   if (g.status && __any(bad) && lane == 0) atomicOr(g.status, (int)HYDRO_STATUS_UNPHYSICAL);
 }
 
+// ---------------------------------------------------------------------------
+// One workgroup of six wavefronts per leaf, for batches that leave the chip
+// idle.  k_step and k_step2 give a leaf to one or two wavefronts, which then
+// take 24 stream positions and 14 faces twice over, one after another: with
+// fewer leaves than SIMDs a substep takes that long however few leaves there
+// are.  Here wavefront w streams the lower or upper half (w & 1) of all 64
+// pencils along axis w >> 1: 10 positions, 5 faces, for every field, as phase
+// Z does.  The x and y differences meet in one LDS accumulator (atomic adds on
+// -0.0, two terms whose order does not matter), the z differences are stored
+// beside it, and after one workgroup barrier wavefronts 0 to 3 finish two
+// planes each with the sum ((x + y) + z) of the other kernels: the same bits.
+// The work per leaf is that of k_step but for one more prologue per column
+// (30 faces and 6 prologues a lane against 28 and 4).
+// ---------------------------------------------------------------------------
+struct LeafLayout {
+  static constexpr int PITCH = ACC_PITCH, PLANE = ACC_PLANE, FIELD = SUB * ACC_PLANE;
+};
+
+template <typename T, int NF, int MODE>
+__global__ void __launch_bounds__(384, sizeof(T) == 4 && NF <= 8 ? 3 : 2) k_leaf(StepArgs s) {
+  using L = LeafLayout;
+  __shared__ __align__(16) double acc[2 * NF * L::FIELD];
+  const GridArgs& g = s.g;
+  const int leaf = s.leaf_base + leaf_of_block(blockIdx.x, g.n_leaves, s.remap);
+  if (leaf >= g.n_leaves) return;  // uniform over the workgroup
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const LeafInfo li = leaf_info(g, leaf);
+  Phys<T> ph;
+  ph.gamma = (T)g.gamma;
+  ph.gm1 = (T)(g.gamma - 1.0);
+  ph.eta1 = (T)g.eta1;
+  const uint32_t fs_b = (uint32_t)((size_t)g.n_leaves * CELLS * sizeof(T));
+  const uint32_t rn_fs = (uint32_t)((size_t)g.n_nodes * CELLS * sizeof(T));
+  const Sources S = make_sources(s.Uk, g.rstate, g.nf, fs_b, rn_fs);
+  bool bad = false;
+  {
+    const int d = wave >> 1, k0 = 4 * (wave & 1);
+    const int a = lane & 7, b = lane >> 3;
+    const Pencil p = make_pencil<T>(li, d, a, b);
+    Ppm<T> st[NF];
+    T qnext[NF];
+    double Hprev[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      st[f] = Ppm<T>{};
+      Hprev[f] = 0.0;
+    }
+    stream_prologue<T, NF>(st, S, p, k0);
+    load_position<T, NF>(S, pencil_src(p, k0 + 5), qnext);
+    for (int j = threadIdx.x; j < NF * L::FIELD / 2; j += 384)
+      reinterpret_cast<double2*>(acc)[j] = make_double2(-0.0, -0.0);
+    __syncthreads();  // the accumulator is clear
+    // cell i along d of the lane's pencil
+    const int off = d == 0 ? b * L::PLANE + a * L::PITCH
+                           : (d == 1 ? b * L::PLANE + a : NF * L::FIELD + b * L::PITCH + a);
+    const int step = d == 0 ? 1 : (d == 1 ? L::PITCH : L::PLANE);
+#pragma unroll 1
+    for (int kk = 5; kk < 10; ++kk) {
+      const int k = k0 + kk;
+      T qn[NF];
+#pragma unroll
+      for (int f = 0; f < NF; ++f) qn[f] = qnext[f];
+      if (kk + 1 < 10) load_position<T, NF>(S, pencil_src(p, k + 1), qnext);
+      T H[NF];
+      stream_step<T, NF>(ph, d, st, qn, H, bad);
+      if (g.reg && (k == 5 || k == TW - 1))
+        record_faces<T, NF, 0, NF>(g, li.leaf, d, k - 5, a, b, H);
+      if (kk >= 6) {
+        double* at = acc + off + (k - 6) * step;
+        if (d < 2) {
+#pragma unroll
+          for (int f = 0; f < NF; ++f)
+            __hip_atomic_fetch_add(&at[f * L::FIELD], (double)H[f] - Hprev[f], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else {
+#pragma unroll
+          for (int f = 0; f < NF; ++f) at[f * L::FIELD] = (double)H[f] - Hprev[f];
+        }
+      }
+#pragma unroll
+      for (int f = 0; f < NF; ++f) Hprev[f] = (double)H[f];
+    }
+  }
+  if (g.status && __any(bad) && lane == 0) atomicOr(g.status, (int)HYDRO_STATUS_UNPHYSICAL);
+  // Uk and U0 of the two cells a finishing lane takes: issued before the wait
+  const int x = lane & 7, y = lane >> 3;
+  const uint32_t leaf_at = (uint32_t)leaf * CELLS + y * 8 + x;
+  const Rsrc U0 = state_rsrc(s.U0 ? s.U0 : s.Uk, (uint32_t)g.nf * fs_b);
+  const Rsrc UO = state_rsrc(s.Uout, (uint32_t)g.nf * fs_b);
+  T ukv[2][NF], u0v[2][NF] = {};
+  if (wave < 4) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t cell_b = (uint32_t)sizeof(T) * (leaf_at + (2 * wave + j) * 64);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) ukv[j][f] = bload(T(), FieldView{S.uk, f * fs_b}, cell_b);
+      if (s.U0) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) u0v[j][f] = bload_once(T(), FieldView{U0, f * fs_b}, cell_b);
+      }
+    }
+  }
+  __syncthreads();  // every flux difference of the leaf is in
+  if (wave >= 4) return;
+  const double dt = *s.dt;
+  const double inv_dx = (double)(SUB * li.blocks);
+  const int lnode = MODE == STEP_RESTRICT ? g.leaf_node[leaf] : -1;
+  double cflmin = INFINITY;
+  const bool rot = g.omega != 0.0;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int z = 2 * wave + j;
+    double* at = acc + z * L::PLANE + y * L::PITCH + x;
+    double src[4] = {0.0, 0.0, 0.0, 0.0};
+    if (rot)
+      rotating_source(g, li, x, y, (double)ukv[j][0], (double)ukv[j][1], (double)ukv[j][2], src);
+    T cv[NF_CORE];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const double sum = at[f * L::FIELD] + at[(NF + f) * L::FIELD];
+      const T o = finish_cell<T>(s, FieldView{UO, f * fs_b}, leaf_at + z * 64, ukv[j][f], u0v[j][f],
+                                 sum, rot && f >= 1 && f <= 4, f >= 1 && f <= 4 ? src[f - 1] : 0.0,
+                                 dt, inv_dx);
+      if (f < NF_CORE) cv[f] = o;
+      if constexpr (MODE == STEP_RESTRICT) {
+        if (lnode >= 0)
+          restrict_out<T, L::PLANE>(s, &at[f * L::FIELD], lnode, f, x, y, z, o);
+      }
+    }
+    if constexpr (MODE == STEP_CFL) cflmin = fmin(cflmin, cfl_quantity<T>(g, cv, 1.0 / inv_dx));
+  }
+  if constexpr (MODE == STEP_CFL) atomic_min_positive(s.dt_next, cflmin, lane);
+}
+
+// Launch of k_leaf for any field count (units k_leaf_f64.hip, k_leaf_f32.hip).
+template <typename T, int MODE>
+inline hipError_t launch_leaf_t(const StepArgs& a, int blocks, hipStream_t st) {
+  switch (a.g.nf) {
+#define OCTOHYDRO_LEAF_CASE(n)                                                             \
+  case n:                                                                                  \
+    hipLaunchKernelGGL((k_leaf<T, n, MODE>), dim3(blocks), dim3(384), 0, st, a);           \
+    return hipGetLastError();
+    OCTOHYDRO_LEAF_CASE(6) OCTOHYDRO_LEAF_CASE(7) OCTOHYDRO_LEAF_CASE(8)
+    OCTOHYDRO_LEAF_CASE(9) OCTOHYDRO_LEAF_CASE(10) OCTOHYDRO_LEAF_CASE(11)
+    OCTOHYDRO_LEAF_CASE(12) OCTOHYDRO_LEAF_CASE(13) OCTOHYDRO_LEAF_CASE(14)
+    OCTOHYDRO_LEAF_CASE(15) OCTOHYDRO_LEAF_CASE(16)
+#undef OCTOHYDRO_LEAF_CASE
+    default: return hipErrorInvalidValue;
+  }
+}
+
 // Launch shape of the fused substep: waves per SIMD (register budget) and
 // wavefronts per leaf (1: k_step; 2: k_step2, species on the second).
 struct StepShape {
@@ -1526,6 +1678,8 @@ hipError_t launch_step_f64_cfl(const StepArgs& a, int blocks, StepShape sh, hipS
 hipError_t launch_step_f32_cfl(const StepArgs& a, int blocks, StepShape sh, hipStream_t st);
 hipError_t launch_step_f64_restrict(const StepArgs& a, int blocks, StepShape sh, hipStream_t st);
 hipError_t launch_step_f32_restrict(const StepArgs& a, int blocks, StepShape sh, hipStream_t st);
+hipError_t launch_leaf_f64(const StepArgs& a, int mode, int blocks, hipStream_t st);
+hipError_t launch_leaf_f32(const StepArgs& a, int mode, int blocks, hipStream_t st);
 hipError_t launch_step3d(const StepArgs& a, int dtype, int blocks, const void* G, int wg,
                          hipStream_t st);
 

@@ -1,5 +1,6 @@
 """Paths of the kernels that the parity suites do not reach by their inputs:
-states far from one in binary32 and binary64 (the range test of the face states)."""
+states far from one in binary32 and binary64 (the range test of the face states), and both sides of
+the batch size below which a leaf gets a workgroup of its own."""
 import numpy as np
 import pytest
 
@@ -114,3 +115,85 @@ def test_unphysical_states_are_reported(env, what, dtype):
     out = grid.empty_state()
     hb.hydro_step(grid, None, torch.from_numpy(U).to("cuda").to(tdt).contiguous(), out, dt, 1.0)
     assert hb.hydro_check_status(grid) == hb.HYDRO_E_UNPHYSICAL
+
+
+def _species(w, nf, seed):
+    rng = np.random.default_rng(seed)
+    extra = [w.U[0] * rng.uniform(0.1, 0.3, size=w.U[0].shape) for _ in range(nf - 6)]
+    return np.ascontiguousarray(np.concatenate([w.U[:6]] + [e[None] for e in extra]))
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("nf,leaf_waves,waves", [(6, 1, 1), (6, 1, 2), (7, 2, 1), (8, 1, 2),
+                                                 (11, 1, 1), (11, 2, 2), (16, 1, 2), (16, 2, 1),
+                                                 (16, 2, 2)])
+def test_launch_shapes_on_a_large_batch(env, nf, leaf_waves, waves, dtype):
+    """Register budgets and wavefronts per leaf on a batch above every size
+    that gives a leaf its own workgroup (4404 leaves, coarser and refined
+    neighbours): binary64 the oracle's bits, binary32 within its rounding."""
+    torch, hb = env
+    print(f"case nf {nf} waves/leaf {leaf_waves} waves/SIMD {waves} dtype {dtype}", flush=True)
+    w = inputs.blobs(base=4, max_level=3)
+    U = _species(w, nf, nf)
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    grid = hb.Grid(w.leaf_coord, w.base, nf, dtype)
+    T = oracle.Table(w.leaf_coord, w.base)
+    keys = (hb.HYDRO_OPT_WAVES_PER_SIMD, hb.HYDRO_OPT_WAVES_PER_LEAF)
+    old = [hb.hydro_get_option(dtype, nf, k) for k in keys]
+    for k, v in zip(keys, (waves, leaf_waves)):
+        hb.hydro_set_option(dtype, nf, k, v)
+    try:
+        dt_o = oracle.cfl_dt(T, U, 0.4)
+        dt = torch.tensor([dt_o], dtype=torch.float64, device="cuda")
+        out = grid.empty_state()
+        hb.hydro_step(grid, None, torch.from_numpy(U).to("cuda").to(tdt).contiguous(), out, dt, 1.0)
+        ref, bad = oracle.step(T, U, dt_o)
+        assert bad == 0
+        got = out.double().cpu().numpy()
+        if dtype == 0:
+            assert np.array_equal(got, ref)
+        else:
+            top = np.abs(ref).reshape(nf, -1).max(1)
+            assert np.all(np.abs(got - ref).reshape(nf, -1).max(1) < 1e-5 * top)
+    finally:
+        for k, v in zip(keys, old):
+            hb.hydro_set_option(dtype, nf, k, v)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("nf", [6, 8, 11, 12, 13, 16])
+@pytest.mark.parametrize("n_leaves", [1, 8, 216, 729, 1000])
+def test_rk3_step_on_both_sides_of_the_whole_leaf_limit(env, n_leaves, nf, dtype):
+    """One chained RK3 step with rotation on uniform boxes from one leaf to
+    past the largest batch that gives each leaf a workgroup: binary64 within
+    1e-12 of the oracle (its bits expected), binary32 within its rounding, and
+    the time step it leaves is the minimum of the state it leaves."""
+    torch, hb = env
+    print(f"case {n_leaves} leaves nf {nf} dtype {dtype}", flush=True)
+    base = round(n_leaves ** (1 / 3))
+    coord = inputs.uniform_leaves(base)
+    w = inputs.random_smooth(coord, base, nf=6, seed=nf)
+    U = _species(w, nf, nf)
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    grid = hb.Grid(coord, base, nf, dtype, omega=0.3, cfl_epilogue=True)
+    T = oracle.Table(coord, base)
+    Un = torch.from_numpy(U).to("cuda").to(tdt).contiguous()
+    W1, W2, out = (grid.empty_state() for _ in range(3))
+    dt = torch.zeros(2, dtype=torch.float64, device="cuda")
+    hb.hydro_cfl_dt(grid, Un, 0.0, dt[1:])
+    hb.hydro_rk3_step(grid, Un, W1, W2, out, 0.4, dt)
+    assert hb.hydro_check_status(grid) == hb.HYDRO_OK
+    got = out.double().cpu().numpy()
+    oracle.set_omega(0.3)
+    try:
+        ref, dt_o, bad = oracle.rk3_step(T, U.astype(got.dtype) if dtype == 0 else
+                                         U.astype(np.float32).astype(np.float64), 0.4)
+    finally:
+        oracle.set_omega(0.0)
+    assert bad == 0
+    top = np.abs(ref).reshape(nf, -1).max(1)
+    err = np.abs(got - ref).reshape(nf, -1).max(1) / top
+    assert np.all(err < (1e-12 if dtype == 0 else 1e-5)), err
+    assert dt[1].item() == oracle.cfl_dt(T, got, 1.0)
+    if dtype == 0:
+        assert dt[0].item() == dt_o
