@@ -47,39 +47,60 @@
 namespace octohydro {
 
 // ---------------------------------------------------------------------------
-// Coarse-fine flux correction: one launch per face orientation o, one thread
-// per (slot, field, coarse face cell); a coarse leaf has at most one slot per
-// orientation, so no two threads of a launch touch the same value.
+// Coarse-fine flux correction, one launch: a thread per (slot, field, coarse
+// face cell).  A cell that lies on several refined faces of its leaf is taken
+// by the thread of the first of them (x, y, z, low before high), which applies
+// all of them in that order, each rounded to the storage type as a launch of
+// its own would store it.  One launch per orientation did the same before, a
+// few microseconds each whatever its size: an RK3 step of an 83-leaf octree
+// went from 142 to 106 us with 15 launches fewer, one of 42,230 leaves and
+// 3,000 slots from 8.76 to 8.69 ms.
 // ---------------------------------------------------------------------------
+
+// First slot of each face orientation, and the slot count in begin[6].
+struct OrientBegin {
+  int32_t begin[7];
+};
 
 template <typename T>
 __global__ void __launch_bounds__(256)
-    k_reflux(GridArgs g, T* __restrict__ Uout, const double* dt, double w, int o, int s0,
-             int n_in_orient) {
-  const int64_t total = (int64_t)n_in_orient * g.nf * 64;
+    k_reflux(GridArgs g, T* __restrict__ Uout, const double* dt, double w, OrientBegin ob) {
+  const int64_t total = (int64_t)ob.begin[6] * g.nf * 64;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= total) return;
   const int uv = (int)(idx & 63);
   const int64_t sf = idx >> 6;
   const int f = (int)(sf % g.nf);
-  const int slot = s0 + (int)(sf / g.nf);
-  const int u = uv & 7, v = uv >> 3;
+  const int slot = (int)(sf / g.nf);
+  int o = 0;
+  while (o < 5 && slot >= ob.begin[o + 1]) ++o;
   const int c = g.slot_leaf[slot];
+  const int32_t* face = g.face_slot + 6 * (size_t)c;
+  // the cell's coordinates: the face's side along its axis, (u, v) across
+  const int d = o >> 1, at = o & 1 ? SUB - 1 : 0, u = uv & 7, v = uv >> 3;
+  const int x = d == 0 ? at : u, y = d == 1 ? at : (d == 0 ? u : v), z = d == 2 ? at : v;
+  for (int q = 0; q < o; ++q) {
+    const int l = q < 2 ? x : (q < 4 ? y : z);
+    if (l == (q & 1 ? SUB - 1 : 0) && face[q] >= 0) return;  // that face's thread does it
+  }
   const double inv_dx = (double)(SUB * (g.base << g.coord[4 * c]));
-  const double* r = g.reg + ((size_t)slot * g.nf + f) * REG_STRIDE;
-  const double hc = r[u + 8 * v];
-  const double* fr = r + REG_COARSE + 2 * u + 16 * (2 * v);
-  const double havg = 0.25 * ((fr[0] + fr[1]) + (fr[16] + fr[17]));
-  const double q = (havg - hc) * inv_dx;
   const double wdt = w * *dt;
-  const int d = o >> 1, side = o & 1;
-  int l[3];
-  l[d] = side ? SUB - 1 : 0;
-  l[d == 0 ? 1 : 0] = u;
-  l[d == 2 ? 1 : 2] = v;
-  T* out = Uout + ((size_t)f * g.n_leaves + c) * CELLS + l[2] * 64 + l[1] * 8 + l[0];
-  const double val = (double)*out;
-  *out = (T)(side ? val - wdt * q : val + wdt * q);
+  T* out = Uout + ((size_t)f * g.n_leaves + c) * CELLS + z * 64 + y * 8 + x;
+  T val = *out;
+  for (int q = o; q < 6; ++q) {
+    const int l = q < 2 ? x : (q < 4 ? y : z);
+    if (l != (q & 1 ? SUB - 1 : 0)) continue;
+    const int sq = face[q];
+    if (sq < 0) continue;
+    const int qu = q < 2 ? y : x, qv = q < 4 ? z : y;
+    const double* r = g.reg + ((size_t)sq * g.nf + f) * REG_STRIDE;
+    const double hc = r[qu + 8 * qv];
+    const double* fr = r + REG_COARSE + 2 * qu + 16 * (2 * qv);
+    const double havg = 0.25 * ((fr[0] + fr[1]) + (fr[16] + fr[17]));
+    const double corr = wdt * ((havg - hc) * inv_dx);
+    val = (T)(q & 1 ? (double)val - corr : (double)val + corr);
+  }
+  *out = val;
 }
 
 // ---------------------------------------------------------------------------
@@ -312,23 +333,21 @@ static GridArgs grid_args(const hydro_grid* gr) {
   return g;
 }
 
-// The flux-correction launches after a substep (nothing without tables).
+// The flux-correction launch after a substep (nothing without tables).
 static int reflux_launch(const hydro_grid* gr, const StepArgs& a, hipStream_t st) {
   if (!a.g.reg) return HYDRO_OK;
   const double w = a.U0 ? a.beta : 1.0;
-  for (int o = 0; o < 6; ++o) {
-    const int s0 = gr->orient_begin[o], n = gr->orient_begin[o + 1] - s0;
-    if (n <= 0) continue;
-    const int64_t total = (int64_t)n * a.g.nf * 64;
-    const int blocks = (int)((total + 255) / 256);
-    if (gr->dtype == HYDRO_F64)
-      hipLaunchKernelGGL(k_reflux<double>, dim3(blocks), dim3(256), 0, st, a.g,
-                         static_cast<double*>(a.Uout), a.dt, w, o, s0, n);
-    else
-      hipLaunchKernelGGL(k_reflux<float>, dim3(blocks), dim3(256), 0, st, a.g,
-                         static_cast<float*>(a.Uout), a.dt, w, o, s0, n);
-    HIP_TRY(hipGetLastError());
-  }
+  OrientBegin ob;
+  for (int o = 0; o < 7; ++o) ob.begin[o] = gr->orient_begin[o];
+  const int64_t total = (int64_t)ob.begin[6] * a.g.nf * 64;
+  const int blocks = (int)((total + 255) / 256);
+  if (gr->dtype == HYDRO_F64)
+    hipLaunchKernelGGL(k_reflux<double>, dim3(blocks), dim3(256), 0, st, a.g,
+                       static_cast<double*>(a.Uout), a.dt, w, ob);
+  else
+    hipLaunchKernelGGL(k_reflux<float>, dim3(blocks), dim3(256), 0, st, a.g,
+                       static_cast<float*>(a.Uout), a.dt, w, ob);
+  HIP_TRY(hipGetLastError());
   return HYDRO_OK;
 }
 

@@ -197,3 +197,40 @@ def test_rk3_step_on_both_sides_of_the_whole_leaf_limit(env, n_leaves, nf, dtype
     assert dt[1].item() == oracle.cfl_dt(T, got, 1.0)
     if dtype == 0:
         assert dt[0].item() == dt_o
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("coarse", [[(1, 1, 1)], [(1, 1, 1), (2, 1, 1), (0, 0, 0)]])
+def test_flux_correction_of_cells_on_several_refined_faces(env, coarse, dtype):
+    """Coarse leaves all but surrounded by refined blocks: their edge and corner
+    cells lie on two and three refined faces and take the corrections in the
+    order x, y, z, low before high.  Binary64 the oracle's bits, binary32
+    within its rounding (a stored value and up to three corrections of it)."""
+    torch, hb = env
+    print(f"case coarse leaves {coarse} dtype {dtype}", flush=True)
+    base = 3
+    rows = []
+    for z, y, x in np.ndindex(base, base, base):
+        if (x, y, z) in coarse:
+            rows.append((0, x, y, z))
+        else:
+            rows += [(1, 2 * x + (q & 1), 2 * y + (q >> 1 & 1), 2 * z + (q >> 2)) for q in range(8)]
+    coord = np.array(rows, np.int32)
+    coord = np.ascontiguousarray(coord[inputs.morton_order(coord)])
+    w = inputs.random_smooth(coord, base, nf=8, seed=3)
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    grid = hb.Grid(coord, base, 8, dtype, reflux=True)
+    assert grid.n_slots
+    T = oracle.Table(coord, base)
+    U = torch.from_numpy(w.U).to("cuda").to(tdt).contiguous()
+    W1, W2, out = (grid.empty_state() for _ in range(3))
+    dt = torch.zeros(1, dtype=torch.float64, device="cuda")
+    hb.hydro_rk3_step(grid, U, W1, W2, out, 0.4, dt)
+    ref, dt_o, bad = oracle.rk3_step(T, U.double().cpu().numpy(), 0.4, reflux=True)
+    assert bad == 0 and dt.item() == dt_o
+    got = out.double().cpu().numpy()
+    if dtype == 0:
+        assert np.array_equal(got, ref)
+    else:
+        top = np.abs(ref).reshape(8, -1).max(1)
+        assert np.all(np.abs(got - ref).reshape(8, -1).max(1) < 5e-6 * top)
