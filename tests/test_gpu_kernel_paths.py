@@ -234,3 +234,29 @@ def test_flux_correction_of_cells_on_several_refined_faces(env, coarse, dtype):
     else:
         top = np.abs(ref).reshape(8, -1).max(1)
         assert np.all(np.abs(got - ref).reshape(8, -1).max(1) < 5e-6 * top)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n_leaves,nf", [(1, 6), (8, 16), (1000, 7), (1331, 6), (4913, 6)])
+def test_totals_over_batches(env, n_leaves, nf, dtype):
+    """Totals over batches below, at and past the number of workgroups per
+    field and the four leaves a workgroup loads at a time, against sums in
+    extended precision: double-double sums leave one rounding of the total,
+    plus one of each product, of random sign."""
+    torch, hb = env
+    base = round(n_leaves ** (1 / 3))
+    print(f"case {n_leaves} leaves nf {nf} dtype {dtype}", flush=True)
+    rng = np.random.default_rng(n_leaves)
+    tdt = np.float64 if dtype == 0 else np.float32
+    U = rng.normal(size=(nf, base ** 3, 8, 8, 8)).astype(tdt)
+    grid = hb.Grid(inputs.uniform_leaves(base), base, nf, dtype)
+    tot = torch.zeros(nf, dtype=torch.float64, device="cuda")
+    also = torch.zeros(nf, dtype=torch.float64, device="cuda")
+    Ud = torch.from_numpy(U).to("cuda")
+    hb.hydro_totals(grid, Ud, tot)
+    hb.hydro_totals_noalloc(grid, Ud, also)
+    dv = (1.0 / (8 * base)) ** 3
+    want = U.astype(np.longdouble).reshape(nf, -1).sum(1) * np.longdouble(dv)
+    scale = np.abs(U.astype(np.float64)).reshape(nf, -1).sum(1) * dv
+    assert np.all(np.abs(tot.cpu().numpy() - want.astype(np.float64)) <= 1e-15 * scale)
+    assert torch.equal(tot, also)
