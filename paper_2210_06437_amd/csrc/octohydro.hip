@@ -376,31 +376,67 @@ static int grid_blocks(int64_t work, int threads, int cap) {
 }
 
 // Ghost fill (hydro_fill_ghosts) into materialised tiles.
-// One workgroup of FILL_THREADS per leaf: 512 keeps as many wavefronts in
-// flight per CU as 256 with half as many leaves, so more of the neighbour
-// cells a tile reads are still in L2 (binary64 6.29 -> 6.04 ms on the
-// 65,535-leaf case, binary32 unchanged; 1024: 6.35 and 4.37 ms).
-constexpr int FILL_THREADS = 512;
-// Each thread takes tile cells t, t + FILL_THREADS, ..., works
-// out where the cell's value comes from once (the leaf itself, a same-level
-// or coarser leaf, or the 8 cells of a refined neighbour's child) and copies
-// or restricts that source in every field.  Consecutive threads hold
-// consecutive tile cells, so a wavefront's writes and most of its reads are
-// contiguous rows.  The tile stores are non-temporal: nothing in this kernel
-// reads a tile again, and streaming the tiles past L2 leaves it to the
-// neighbour cells that other tiles read (65,535-leaf case: 7.85 -> 6.29 ms
-// in binary64, 4.85 -> 3.93 ms in binary32, fetched bytes 20.6 -> 16.0 GB;
-// fewer workgroups per CU, for a smaller working set, measured slower).
+// One workgroup of FILL_THREADS per leaf (65,535 leaves of 11 fields, binary64
+// and binary32: 256 threads 5.74 and 2.96 ms, 512 5.81 and 3.06, 1024 6.19 and
+// 3.53).
+constexpr int FILL_THREADS = 256;
+// The cells of a tile in the order of their sources: region by region (the
+// leaf, then the 26 neighbours), each in the order of its cells in memory, so
+// that consecutive threads read consecutive cells of one block.
+struct FillOrder {
+  uint16_t cell[TILE];
+  constexpr FillOrder() : cell() {
+    int n = 0;
+    for (int q = 0; q < 27; ++q) {
+      const int slot = q == 0 ? 13 : (q <= 13 ? q - 1 : q);
+      int lo[3] = {}, hi[3] = {};
+      const int r[3] = {slot % 3 - 1, (slot / 3) % 3 - 1, slot / 9 - 1};
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = r[k] < 0 ? 0 : (r[k] == 0 ? GH : GH + SUB);
+        hi[k] = r[k] < 0 ? GH : (r[k] == 0 ? GH + SUB : TW);
+      }
+      for (int z = lo[2]; z < hi[2]; ++z)
+        for (int y = lo[1]; y < hi[1]; ++y)
+          for (int x = lo[0]; x < hi[0]; ++x) cell[n++] = (uint16_t)((z * TW + y) * TW + x);
+    }
+  }
+};
+static __device__ const FillOrder fill_order;
+
+// Each thread works out where its cells (of the order above) come from
+// once -- the leaf, a same-level or coarser leaf's cell, or the first of the 8
+// cells of a refined neighbour's child -- and then goes field by field: the
+// values are gathered into an LDS tile while the next field's loads are
+// issued, and the tile is written out 16 bytes a thread.  What bounds it is
+// the number of 64-byte pieces the L1 works through: gathered in the order of
+// the tile, a wavefront's 64 cells lay in some 14 rows and neighbours, and the
+// L1 was busy or waiting on its own misses all of the time (L1 accesses per
+// leaf 22 k, 24 k in binary32; now 15 k and 14 k); in the order of the sources
+// they lie in one to a few.  65,535 leaves of 11 fields: binary64 6.03 -> 5.74
+// ms, now near the rate of a large copy (16.6 GB written, 10 GB fetched),
+// binary32 3.86 -> 2.96 ms; 5,628 leaves of 11 binary64 fields 447 -> 334 us,
+// 6,966 of 8 binary32 267 -> 157 us.  The fields in groups over the grid, for
+// a smaller working set in L2, were slower (2 groups 5.89 ms, 4 groups 6.41,
+// 11 groups 8.56), and so were ordinary stores (6.06 ms).  The tile stores are non-temporal: nothing here reads a tile again,
+// and L2 is left to the neighbour cells that other tiles read.
+constexpr int FILL_SLOTS = (TILE + FILL_THREADS - 1) / FILL_THREADS;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 template <typename T>
 __global__ void __launch_bounds__(FILL_THREADS) k_fill(GridArgs g, const T* __restrict__ U,
-                                              T* __restrict__ G, int remap) {
+                                              T* __restrict__ G, int remap, int wide) {
+  __shared__ __align__(16) T tile[2][TILE];
   const int leaf = leaf_of_block(blockIdx.x, g.n_leaves, remap);
   const int4 c4 = reinterpret_cast<const int4*>(g.coord)[leaf];
   const int ic[3] = {c4.y, c4.z, c4.w};
   const int blocks = g.base << c4.x;
   const size_t fsU = (size_t)g.n_leaves * CELLS, fsG = (size_t)g.n_leaves * TILE;
-  T* __restrict__ Gl = G + (size_t)leaf * TILE;
-  for (int t = threadIdx.x; t < TILE; t += blockDim.x) {
+  uint32_t src[FILL_SLOTS];  // cell index within a field array
+  int dst[FILL_SLOTS];       // tile cell; with bit 16 set where 8 cells are averaged
+#pragma unroll
+  for (int j = 0; j < FILL_SLOTS; ++j) {
+    const int i = threadIdx.x + j * FILL_THREADS;
+    const int t = fill_order.cell[i < TILE ? i : TILE - 1];
     const int tp[3] = {t % TW, (t / TW) % TW, t / (TW * TW)};
     int r[3], l[3];
 #pragma unroll
@@ -411,33 +447,58 @@ __global__ void __launch_bounds__(FILL_THREADS) k_fill(GridArgs g, const T* __re
     const int slot = (r[2] + 1) * 9 + (r[1] + 1) * 3 + (r[0] + 1);
     const int kind = slot == 13 ? (int)HYDRO_SAME_LEAF : (int)g.kind[27 * leaf + slot];
     const int id = slot == 13 ? leaf : g.nbr[27 * leaf + slot];
+    dst[j] = t;
     if (kind == HYDRO_SAME_REFINED) {
-      for (int f = 0; f < g.nf; ++f)
-        __builtin_nontemporal_store(
-            neighbour_value<T>(g, U + f * fsU, leaf, ic, blocks, kind, id, r, l), &Gl[f * fsG + t]);
+      // child (l >> 2) on each axis, fine cells from (2 l) & 7
+      const int child =
+          g.children[8 * id + (l[2] >> 2) * 4 + (l[1] >> 2) * 2 + (l[0] >> 2)];
+      src[j] = (uint32_t)child * CELLS + ((2 * l[2]) & 7) * 64 + ((2 * l[1]) & 7) * 8 +
+               ((2 * l[0]) & 7);
+      dst[j] |= 1 << 16;
     } else {
-      // a copy: the cell itself, a same-level cell or the covering coarse
-      // cell; every field's load is issued before the first store
-      const T* __restrict__ src = U;
-      size_t o;
-      if (kind == HYDRO_SAME_LEAF) {
-        o = (size_t)id * CELLS + l[2] * 64 + l[1] * 8 + l[0];
-      } else {
-        int c[3];
+      int c[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const int nb = wrap(ic[k] + r[k], blocks);
-          c[k] = 4 * (nb & 1) + (l[k] >> 1);
-        }
-        o = (size_t)id * CELLS + c[2] * 64 + c[1] * 8 + c[0];
+      for (int k = 0; k < 3; ++k) {
+        const int nb = wrap(ic[k] + r[k], blocks);
+        c[k] = kind == HYDRO_COARSER_LEAF ? 4 * (nb & 1) + (l[k] >> 1) : l[k];
       }
-      T v[16];
+      src[j] = (uint32_t)id * CELLS + c[2] * 64 + c[1] * 8 + c[0];
+    }
+  }
+  T* __restrict__ Gl = G + (size_t)leaf * TILE;
+  T v[FILL_SLOTS];
+  for (int f = 0; f <= g.nf; ++f) {
+    if (f > 0) {
+      // field f - 1, gathered before, goes into its LDS tile
+      T* tl = tile[f & 1];
 #pragma unroll
-      for (int f = 0; f < 16; ++f)
-        if (f < g.nf) v[f] = src[f * fsU + o];
+      for (int j = 0; j < FILL_SLOTS; ++j)
+        if (j + 1 < FILL_SLOTS || threadIdx.x + j * FILL_THREADS < TILE) tl[dst[j] & 0xFFFF] = v[j];
+      __syncthreads();
+    }
+    if (f < g.nf) {
+      const T* __restrict__ u = U + f * fsU;
 #pragma unroll
-      for (int f = 0; f < 16; ++f)
-        if (f < g.nf) __builtin_nontemporal_store(v[f], &Gl[f * fsG + t]);
+      for (int j = 0; j < FILL_SLOTS; ++j) {
+        const T* __restrict__ P = u + src[j];
+        if (dst[j] >> 16)
+          v[j] = T(0.125) * (((P[0] + P[1]) + (P[8] + P[9])) + ((P[64] + P[65]) + (P[72] + P[73])));
+        else
+          v[j] = P[0];
+      }
+    }
+    if (f > 0) {
+      const T* tl = tile[f & 1];
+      T* out = Gl + (f - 1) * fsG;
+      if (wide) {
+        constexpr int N = 16 / sizeof(T);
+        for (int i = threadIdx.x; i < TILE / N; i += FILL_THREADS)
+          __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(tl)[i],
+                                      reinterpret_cast<u32x4*>(out) + i);
+      } else {
+        for (int i = threadIdx.x; i < TILE; i += FILL_THREADS)
+          __builtin_nontemporal_store(tl[i], out + i);
+      }
     }
   }
 }
@@ -450,12 +511,14 @@ __global__ void __launch_bounds__(FILL_THREADS) k_fill(GridArgs g, const T* __re
 constexpr int FILL_REMAP = 1;
 static int fill_launch(const hydro_grid* gr, const void* U, void* G, hipStream_t st) {
   const GridArgs g = grid_args(gr);
+  // tiles are multiples of 16 bytes, so G's own alignment decides
+  const int wide = (reinterpret_cast<uintptr_t>(G) & 15) == 0;
   if (gr->dtype == HYDRO_F64)
     hipLaunchKernelGGL(k_fill<double>, dim3(g.n_leaves), dim3(FILL_THREADS), 0, st, g,
-                       static_cast<const double*>(U), static_cast<double*>(G), FILL_REMAP);
+                       static_cast<const double*>(U), static_cast<double*>(G), FILL_REMAP, wide);
   else
     hipLaunchKernelGGL(k_fill<float>, dim3(g.n_leaves), dim3(FILL_THREADS), 0, st, g,
-                       static_cast<const float*>(U), static_cast<float*>(G), FILL_REMAP);
+                       static_cast<const float*>(U), static_cast<float*>(G), FILL_REMAP, wide);
   HIP_TRY(hipGetLastError());
   return HYDRO_OK;
 }

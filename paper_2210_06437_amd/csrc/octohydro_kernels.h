@@ -63,44 +63,6 @@ __device__ __forceinline__ int wrap(int a, int m) {
 }
 
 // ---------------------------------------------------------------------------
-// Ghost values (Sec. VI): same-level copy, injection from a coarser leaf, or
-// restriction (mean of the 8 covering cells) from a refined neighbour.
-// ---------------------------------------------------------------------------
-
-// Value of the neighbour-side cell with local coordinates l[3] in [0,8) of
-// the neighbour block in direction r[3] (each in {-1,0,1}) of `leaf`.
-template <typename T>
-__device__ __forceinline__ T neighbour_value(const GridArgs& g, const T* __restrict__ Uf, int leaf,
-                                             const int (&ic)[3], int blocks, int kind, int id,
-                                             const int (&r)[3], const int (&l)[3]) {
-  if (kind == HYDRO_SAME_LEAF) {
-    return Uf[(size_t)id * CELLS + l[2] * 64 + l[1] * 8 + l[0]];
-  }
-  if (kind == HYDRO_COARSER_LEAF) {
-    int c[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const int nb = wrap(ic[k] + r[k], blocks);
-      c[k] = 4 * (nb & 1) + (l[k] >> 1);
-    }
-    return Uf[(size_t)id * CELLS + c[2] * 64 + c[1] * 8 + c[0]];
-  }
-  // refined neighbour: child (l >> 2) on each axis, fine cells (2l + bit) & 7
-  const int child = g.children[8 * id + (l[2] >> 2) * 4 + (l[1] >> 2) * 2 + (l[0] >> 2)];
-  const T* __restrict__ P = Uf + (size_t)child * CELLS;
-  const int fx0 = (2 * l[0]) & 7, fy0 = (2 * l[1]) & 7, fz0 = (2 * l[2]) & 7;
-  const T v000 = P[fz0 * 64 + fy0 * 8 + fx0];
-  const T v100 = P[fz0 * 64 + fy0 * 8 + fx0 + 1];
-  const T v010 = P[fz0 * 64 + (fy0 + 1) * 8 + fx0];
-  const T v110 = P[fz0 * 64 + (fy0 + 1) * 8 + fx0 + 1];
-  const T v001 = P[(fz0 + 1) * 64 + fy0 * 8 + fx0];
-  const T v101 = P[(fz0 + 1) * 64 + fy0 * 8 + fx0 + 1];
-  const T v011 = P[(fz0 + 1) * 64 + (fy0 + 1) * 8 + fx0];
-  const T v111 = P[(fz0 + 1) * 64 + (fy0 + 1) * 8 + fx0 + 1];
-  return T(0.125) * (((v000 + v100) + (v010 + v110)) + ((v001 + v101) + (v011 + v111)));
-}
-
-// ---------------------------------------------------------------------------
 // Restricted copies of the refined nodes (the coarse side of a coarse-fine
 // face, Sec. VI): coarse cell (x, y, z) of node n is the mean of the 8 cells
 // of child (x>>2, y>>2, z>>2) that cover it, summed in the same fixed order as

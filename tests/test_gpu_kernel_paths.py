@@ -260,3 +260,39 @@ def test_totals_over_batches(env, n_leaves, nf, dtype):
     scale = np.abs(U.astype(np.float64)).reshape(nf, -1).sum(1) * dv
     assert np.all(np.abs(tot.cpu().numpy() - want.astype(np.float64)) <= 1e-15 * scale)
     assert torch.equal(tot, also)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("nf", [6, 11, 16])
+@pytest.mark.parametrize("shift", [0, 1, 2])
+def test_ghost_fill_at_any_alignment(env, shift, nf, dtype):
+    """Tiles written to buffers that are not 16-byte aligned, and input states
+    that are not, on a tree with coarser and refined neighbours: binary64 the
+    oracle's bits, binary32 the bits of its own aligned call and within a
+    rounding of each mean."""
+    torch, hb = env
+    print(f"case shift {shift} nf {nf} dtype {dtype}", flush=True)
+    w = inputs.blobs(base=2, max_level=2, threshold=0.5)
+    U = _species(w, nf, nf)
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    grid = hb.Grid(w.leaf_coord, w.base, nf, dtype)
+    src = torch.from_numpy(U).to("cuda").to(tdt).contiguous()
+    shape = (nf, w.n_leaves, 14, 14, 14)
+    n = int(np.prod(shape))
+    buf = torch.full((n + 4,), -7.0, dtype=tdt, device="cuda")
+    inb = torch.zeros(src.numel() + 4, dtype=tdt, device="cuda")
+    inb[shift:shift + src.numel()] = src.reshape(-1)
+    G = buf[shift:shift + n].view(shape)
+    hb.hydro_fill_ghosts(grid, inb[shift:shift + src.numel()].view(src.shape), G)
+    want = oracle.fill_ghosts(oracle.Table(w.leaf_coord, w.base), src.double().cpu().numpy())
+    got = G.double().cpu().numpy()
+    if dtype == 0:
+        assert np.array_equal(got, want)
+    else:
+        assert np.all(np.abs(got - want) <= 3e-7 * np.abs(want).reshape(nf, -1).max(1)
+                      .reshape(nf, 1, 1, 1, 1))
+        plain = torch.empty(shape, dtype=tdt, device="cuda")
+        hb.hydro_fill_ghosts(grid, src, plain)
+        assert torch.equal(plain, G)
+    rest = torch.cat([buf[:shift], buf[shift + n:]])
+    assert torch.all(rest == -7.0)
