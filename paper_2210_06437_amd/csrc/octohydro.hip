@@ -554,12 +554,13 @@ struct Options {
 // Later-stage substep of 27,649 leaves, us, with one wavefront per leaf at one
 // or two per SIMD (512 or 256 registers) and with the species on a second
 // wavefront:
-//   binary64, fields  6: 939  963     -    10: 1812  1867  1673
-//                     7: 1337 1114 1457    11: 1971  2839  1797
-//                     8: 1502 1285 1516    14: 2558  7020  2214
-//                     9: 1676 1468 1588    15: 2861  8852  2483 (256 registers)
-//   binary32          9: 798   806  828    11: 1009  1009   941
-//                    10: 873   881  881    16: 1736  2154  1462
+//   binary64, fields  6: 905  901     -    10: 1815  2176  1616
+//                     7: 1340 1096 1364    11: 1974  3197  1736
+//                     8: 1507 1262 1435    14: 2600  7020  2231
+//                     9: 1674 1472 1522    15: 2861  8852  2468 (256 registers)
+//   binary32          8: 674   682  706    10: 848   834   822
+//                     9: 775   758  762    11: 975   942   893
+// (binary32, 9 fields, 1000 leaves: 41, 42, 37).
 // Up to the field count whose state fits 256 registers with few spills one
 // wavefront holds all fields; beyond it the second wavefront's barrier each
 // step costs less than the spills or the lower occupancy.  6 binary64 and all
@@ -570,7 +571,7 @@ static Options default_options(int dtype, int nf) {
     o.waves_per_leaf = nf >= 10 ? 2 : 1;
     o.waves_per_simd = (nf >= 7 && nf <= 9) || nf >= 15 ? 2 : 1;
   } else {
-    o.waves_per_leaf = nf >= 11 ? 2 : 1;
+    o.waves_per_leaf = nf >= 9 ? 2 : 1;
   }
   return o;
 }

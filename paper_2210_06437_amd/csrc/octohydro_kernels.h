@@ -978,7 +978,7 @@ __device__ __forceinline__ void stream_step(const Phys<T>& ph, int d, Ppm<T> (&s
 // binary64 addition (it keeps the sign of a zero term) and a sum of two terms
 // does not depend on their order, so the accumulator holds exactly dHx + dHy
 // whichever lane gets there first, with no branch on the lane.
-template <typename T, int NF, int AP>
+template <typename T, int NF, int XU, int AP>
 __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, const LeafInfo& li,
                                          double* __restrict__ acc, int h, int lane, bool& bad) {
   const GridArgs& g = s.g;
@@ -1007,7 +1007,7 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
   stream_prologue<T, NF>(st, S, p, 0);
   T qnext[NF];
   load_position<T, NF>(S, pencil_src(p, 5), qnext);
-#pragma unroll 1
+#pragma unroll XU
   for (int k = 5; k < TW; ++k) {
     T qn[NF];
 #pragma unroll
@@ -1036,10 +1036,7 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
 // Phase Z of half h: lane (x, y) streams its z-pencil over stream positions
 // [4h, 4h+10), which yields the z-faces of cells z in [4h, 4h+4), adds dHz
 // to the accumulator and finishes those cells.  ZU: unroll factor of the
-// stream loop.  Unrolled by 2, consecutive steps keep the stream state in
-// alternating registers instead of copying it back at every step: with the
-// 512-register budget that was 2-3 % faster in binary64 (the same bits); at
-// two wavefronts per SIMD it was 1 % slower.
+// stream loop (see k_step).
 template <typename T, int NF, int MODE, int ZU, int AP>
 __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, const LeafInfo& li,
                                         double* __restrict__ acc, int h, int lane, double dt, double inv_dx, bool& bad,
@@ -1125,6 +1122,18 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
 template <typename T, int NF, int W, int MODE>
 __global__ void __launch_bounds__(64, W) k_step(StepArgs s) {
   constexpr int AP = W == 2 ? 8 : 9;  // accumulator row pitch (see AccLayout)
+  // Unroll factors of the stream loops of phases XY and Z (9 and 5 are whole).
+  // Unrolled, the recurrence moves to other registers instead of being copied
+  // (each field's 4 values a step), and where a position is read from is known
+  // at compile time.  Rolled and whole at 27,649 leaves, us: 948 and 905
+  // (binary64, 6 fields), 493 and 480 (binary32, 6), 686 and 674 (binary32, 8).
+  // With more binary64 fields the state fills the registers and whole spills:
+  // 8 fields at 256 registers 1279 rolled, 1262 by 3 and 1, 1299 whole (9: 1472
+  // rolled, 1485 by 3); 11 fields at 512 registers 1968 rolled with phase Z by
+  // 2, 1974 with phase XY by 3, 2337 whole.
+  constexpr bool WHOLE = sizeof(T) == 4 || NF == NF_CORE;
+  constexpr int XU = WHOLE ? 9 : (W == 2 && NF <= 8 ? 3 : 1);
+  constexpr int ZU = WHOLE ? 5 : (W == 2 ? 1 : 2);
   __shared__ __align__(16) double acc[NF * AccLayout<AP>::HALF];
   const GridArgs& g = s.g;
   const int leaf = s.leaf_base + leaf_of_block(blockIdx.x, g.n_leaves, s.remap);
@@ -1144,9 +1153,9 @@ __global__ void __launch_bounds__(64, W) k_step(StepArgs s) {
   const int lnode = MODE == STEP_RESTRICT ? g.leaf_node[leaf] : -1;
 #pragma unroll 1
   for (int h = 0; h < 2; ++h) {
-    phase_xy<T, NF, AP>(s, ph, li, acc, h, fresh(lane), bad);
+    phase_xy<T, NF, XU, AP>(s, ph, li, acc, h, fresh(lane), bad);
     wave_lds_sync();
-    phase_z<T, NF, MODE, W == 1 ? 2 : 1, AP>(s, ph, li, acc, h, fresh(lane), dt, inv_dx, bad,
+    phase_z<T, NF, MODE, ZU, AP>(s, ph, li, acc, h, fresh(lane), dt, inv_dx, bad,
                                              cflmin, lnode);
     wave_lds_sync();
   }
@@ -1247,6 +1256,14 @@ __device__ __forceinline__ void group_step(const Phys<T>& ph, int d, Ppm<T> (&st
   }
 }
 
+// Whether k_step2's stream loops are unrolled whole (see k_step).  Rolled and
+// whole at 27,649 leaves, us: 1787 and 1736 (binary64, 11 fields), 2068 and 2019
+// (13), 2231 and 2992 (14: spills), 940 and 893 (binary32, 11), 1461 and 1395 (16).
+template <typename T, int NF>
+__device__ constexpr bool unroll_group() {
+  return sizeof(T) == 4 || NF <= 13;
+}
+
 // Phase XY of half h for one field group (see phase_xy).
 template <typename T, int NF, int F0, int NG>
 __device__ __forceinline__ void phase_xy_group(const StepArgs& s, const Phys<T>& ph,
@@ -1279,7 +1296,8 @@ __device__ __forceinline__ void phase_xy_group(const StepArgs& s, const Phys<T>&
   prologue_group<T, F0, NG>(st, S, p, 0);
   T qnext[NG];
   load_group<T, F0, NG>(S, pencil_src(p, 5), qnext);
-#pragma unroll 1
+  constexpr int U = unroll_group<T, NF>() ? 9 : 1;
+#pragma unroll U
   for (int k = 5; k < TW; ++k) {
     T qn[NG];
 #pragma unroll
@@ -1336,7 +1354,8 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
   prologue_group<T, F0, NG>(st, S, p, k0);
   T qnext[NG];
   load_group<T, F0, NG>(S, pencil_src(p, k0 + 5), qnext);
-#pragma unroll 1
+  constexpr int U = unroll_group<T, NF>() ? 5 : 1;
+#pragma unroll U
   for (int kk = 5; kk < 10; ++kk) {
     const int k = k0 + kk;
     T qn[NG];
@@ -1494,7 +1513,11 @@ __global__ void __launch_bounds__(384, sizeof(T) == 4 && NF <= 8 ? 3 : 2) k_leaf
     const int off = d == 0 ? b * L::PLANE + a * L::PITCH
                            : (d == 1 ? b * L::PLANE + a : NF * L::FIELD + b * L::PITCH + a);
     const int step = d == 0 ? 1 : (d == 1 ? L::PITCH : L::PLANE);
-#pragma unroll 1
+    // whole (see k_step) while nothing spills: 8 leaves, us, rolled and whole,
+    // 17.2 and 15.6 (binary64, 8 fields), 21.7 and 21.3 (11; 512 leaves 49.2
+    // and 52.7), 27.7 and 30.0 (13), 14.4 and 13.8 (binary32, 11)
+    constexpr int U = sizeof(T) == 4 || NF <= 9 ? 5 : 1;
+#pragma unroll U
     for (int kk = 5; kk < 10; ++kk) {
       const int k = k0 + kk;
       T qn[NF];
