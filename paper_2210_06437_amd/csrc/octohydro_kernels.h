@@ -106,20 +106,13 @@ __global__ void __launch_bounds__(512)
 // Keeps a value's computation ahead of this point in program order: an
 // empty statement on a register (no instruction, no memory access).  The
 // instruction selector otherwise orders pure arithmetic its own way and
-// computes values long before their use, which holds registers: in the
-// fused substep's stream step, binary64 at 11 fields took 420 registers
-// with 179 AGPR moves per z-stream step and 356 with 68 with the pins.
-// For 8-byte values the statement is volatile, which also keeps memory
-// accesses from moving across it; for 4-byte values it is not, which lets
-// the next group's loads start earlier: the binary32 3D step took 27.5 ms
-// instead of 30.2, while the binary64 one was 1 % faster with the volatile
-// form and the substep kernel the same either way (the same bits in all).
+// computes values long before their use, which holds registers.  Not
+// volatile, so that the next group's loads may start earlier: with a volatile
+// statement the binary64 3D substep of 3,100 leaves took 5.09 ms instead of
+// 4.94 and the axis kernels the same (the same bits in all).
 template <typename T>
 __device__ __forceinline__ void keep_order(T& v) {
-  if constexpr (sizeof(T) == 4)
-    asm("" : "+v"(v));
-  else
-    asm volatile("" : "+v"(v));
+  asm("" : "+v"(v));
 }
 
 template <typename T>

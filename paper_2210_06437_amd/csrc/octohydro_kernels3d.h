@@ -94,15 +94,25 @@ __device__ __forceinline__ constexpr PointLine face_point(int sd, int pu, int pv
 // and 16 are exact, so each FMA rounds once, as the addition does; the
 // division is by the reciprocal with Markstein's residual correction, which
 // gives the correctly rounded quotient in 3 instructions.
-__device__ __forceinline__ double simpson_close(double corners, double edges, double centre) {
-  const double x = fma(16.0, centre, fma(4.0, edges, corners));
+__device__ __forceinline__ double simpson_edges(double corners, double edges) {
+  return fma(4.0, edges, corners);
+}
+__device__ __forceinline__ float simpson_edges(float corners, float edges) {
+  return fmaf(4.0f, edges, corners);
+}
+__device__ __forceinline__ double simpson_centre(double corners_edges, double centre) {
+  const double x = fma(16.0, centre, corners_edges);
   const double q = x * (1.0 / 36.0);
   return fma(fma(-36.0, q, x), 1.0 / 36.0, q);
 }
-__device__ __forceinline__ float simpson_close(float corners, float edges, float centre) {
-  const float x = fmaf(16.0f, centre, fmaf(4.0f, edges, corners));
+__device__ __forceinline__ float simpson_centre(float corners_edges, float centre) {
+  const float x = fmaf(16.0f, centre, corners_edges);
   const float q = x * (1.0f / 36.0f);
   return fmaf(fmaf(-36.0f, q, x), 1.0f / 36.0f, q);
+}
+template <typename T>
+__device__ __forceinline__ T simpson_close(T corners, T edges, T centre) {
+  return simpson_centre(simpson_edges(corners, edges), centre);
 }
 
 // Simpson combination of the 9 point values of one field, points in the
@@ -116,9 +126,10 @@ __device__ __forceinline__ T simpson9(const T (&h)[9]) {
 
 // Flux of all fields through the face between tile cells tl and tl + stride
 // of D (Gt: field 0's tile of the leaf, field stride fsG).  The core fields'
-// end values at all 9 points are read first (their loads are independent, so
-// many are in flight at once) and give the points' Kurganov-Tadmor fluxes,
-// velocities and signal speeds; each passive field then uses those speeds.
+// ends give the points' Kurganov-Tadmor fluxes, which go into running Simpson
+// sums pair by pair (2 values a field live instead of 9: 206 registers
+// instead of 243 at 11 binary64 fields), and the points' velocities and
+// signal speeds, which each passive field then uses.
 template <typename T, int NF, int D>
 __device__ __forceinline__ void face_flux_3d(const Phys<T>& ph, const T* __restrict__ Gt,
                                              size_t fsG, int tl, T (&H)[NF], bool& bad) {
@@ -126,29 +137,38 @@ __device__ __forceinline__ void face_flux_3d(const Phys<T>& ph, const T* __restr
   constexpr int PU[9] = {-1, 1, 1, -1, 0, 0, -1, 1, 0};
   constexpr int PV[9] = {-1, 1, -1, 1, -1, 1, 0, 0, 0};
   const int tr = tl + SD;
-  T hc[NF_CORE][9], vl[9], vr[9], ha[9];
+  T ca[NF_CORE], ed[NF_CORE], vl[9], vr[9], ha[9];  // corner and edge sums
 #pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    const PointLine pl = face_point<D>(1, PU[q], PV[q]);
-    const PointLine pr = face_point<D>(-1, PU[q], PV[q]);
-    T UL[NF_CORE], UR[NF_CORE], Hc[NF_CORE];
+  for (int p = 0; p < 5; ++p) {  // the points in pairs, the centre alone
+    T h[2][NF_CORE];
+#pragma unroll
+    for (int i = 0; i < (p < 4 ? 2 : 1); ++i) {
+      const int q = 2 * p + i;
+      const PointLine pl = face_point<D>(1, PU[q], PV[q]);
+      const PointLine pr = face_point<D>(-1, PU[q], PV[q]);
+      T UL[NF_CORE], UR[NF_CORE];
+#pragma unroll
+      for (int f = 0; f < NF_CORE; ++f) {
+        UL[f] = line_end(Gt + f * fsG + tl, pl.s, pl.right);
+        UR[f] = line_end(Gt + f * fsG + tr, pr.s, pr.right);
+      }
+      core_flux(ph, D, UL, UR, h[i], vl[q], vr[q], ha[q], bad);
+#pragma unroll
+      for (int f = 0; f < NF_CORE; ++f) keep_order(h[i][f]);
+      keep_order(vl[q]);
+      keep_order(vr[q]);
+      keep_order(ha[q]);
+    }
 #pragma unroll
     for (int f = 0; f < NF_CORE; ++f) {
-      UL[f] = line_end(Gt + f * fsG + tl, pl.s, pl.right);
-      UR[f] = line_end(Gt + f * fsG + tr, pr.s, pr.right);
+      if (p == 0) ca[f] = h[0][f] + h[1][f];
+      else if (p == 1) ca[f] = ca[f] + (h[0][f] + h[1][f]);
+      else if (p == 2) ed[f] = h[0][f] + h[1][f];
+      else if (p == 3) ed[f] = ed[f] + (h[0][f] + h[1][f]);
+      else H[f] = simpson_close(ca[f], ed[f], h[0][f]);
+      keep_order(p < 2 ? ca[f] : (p < 4 ? ed[f] : H[f]));
     }
-    core_flux(ph, D, UL, UR, Hc, vl[q], vr[q], ha[q], bad);
-#pragma unroll
-    for (int f = 0; f < NF_CORE; ++f) {
-      hc[f][q] = Hc[f];
-      keep_order(hc[f][q]);
-    }
-    keep_order(vl[q]);
-    keep_order(vr[q]);
-    keep_order(ha[q]);
   }
-#pragma unroll
-  for (int f = 0; f < NF_CORE; ++f) H[f] = simpson9(hc[f]);
 #pragma unroll
   for (int f = NF_CORE; f < NF; ++f) {
     T h[9];
@@ -180,10 +200,8 @@ __device__ __forceinline__ constexpr int tile_at(int x, int y, int z) {
 // z-face is the high z-face of the plane before (z-face 0 comes from the
 // first pass).  The differences are summed ((x + y) + z) in binary64 and the
 // cell is finished as k_step does.
-// binary64 runs at 1 wavefront per SIMD, two z-halves of three loops (one
-// face orientation per loop): one face evaluation nearly fills the 512
-// registers, and three of them in one loop body spilled 333 VGPRs to memory
-// (80 in this layout; 110.7 vs 122.3 ms on the 65535-leaf case).  binary32
+// binary64 runs in two z-halves of three loops, one face orientation per
+// loop, at 1 wavefront per SIMD (its LDS allows 4 a CU at 11 fields).  binary32
 // runs at 2 wavefronts per SIMD (256 VGPRs; 63 ms vs 89 ms at 1) as one
 // sweep with the three faces in one loop body, whose LDS (11 KB) keeps 8
 // wavefronts per CU where the binary64 layout's 39 KB would allow 4.
@@ -426,7 +444,7 @@ constexpr size_t wg3d_lds_bytes() {
 // face fluxes: thread t of the 256 takes cells t and t + 256, each with the
 // binary64 sums ((xhi - xlo) + (yhi - ylo)) + (zhi - zlo) from the flux
 // store Hs (the layout of k_step3d_wg).
-template <typename T, int NF, int P>
+template <typename T, int NF, int N, int P>
 __device__ __forceinline__ void finish_leaf_3d(const StepArgs& s, const T (&Hs)[P][NF][64],
                                                int leaf, int4 c4) {
   const GridArgs& g = s.g;
@@ -440,7 +458,7 @@ __device__ __forceinline__ void finish_leaf_3d(const StepArgs& s, const T (&Hs)[
   const T* __restrict__ Uk = static_cast<const T*>(s.Uk);
   const T* __restrict__ U0 = static_cast<const T*>(s.U0);
 #pragma unroll 1
-  for (int c = threadIdx.x; c < CELLS; c += 256) {
+  for (int c = threadIdx.x; c < CELLS; c += N) {
     const int x = c & 7, y = (c >> 3) & 7, z = c >> 6;
     const int xy = y * 8 + x;
     const uint32_t at = (uint32_t)leaf * CELLS + c;
@@ -525,7 +543,7 @@ __global__ void __launch_bounds__(256, 1) k_step3d_wg(StepArgs s, const T* __res
   }
   if (g.status && __any(bad) && lane == 0) atomicOr(g.status, (int)HYDRO_STATUS_UNPHYSICAL);
   __syncthreads();
-  finish_leaf_3d<T, NF, FACE_PLANES>(s, Hs, leaf, c4);
+  finish_leaf_3d<T, NF, 256, FACE_PLANES>(s, Hs, leaf, c4);
 }
 
 // ---------------------------------------------------------------------------
@@ -544,18 +562,29 @@ __global__ void __launch_bounds__(256, 1) k_step3d_wg(StepArgs s, const T* __res
 //  - Boundary task: face 0 or face 8 along x or y for the whole leaf, one
 //    face per lane, evaluated as in k_step3d_wg (both sides' line ends).
 //  - Column task: lane (x, y) walks up its column, carrying the right ends
-//    of the 9 lines a x + b y + z of the cell below; face c - 1/2 takes the
+//    of lines a x + b y + z of the cell below; face c - 1/2 takes the
 //    carried end of e(a, b) and the left end of e(-a, -b) of cell c at point
-//    (a, b).  Two tasks split the column: faces 0..3 and 4..8.
+//    (a, b).  binary64 walks it in four passes over groups of points, binary32
+//    once over all 9 (ws_column, ws_column_carry).
 // The column task walks its lines in the direction of the face normal, not
 // always in the canonical direction of the point, and parabola() gives the
 // same ends either way.  The points are taken in pairs (a, b) and (-a, -b),
 // whose two lines give both points' states, or in the plane task by line
 // group, in the order of the Simpson sums, so each face's flux is the
 // sequence of operations face_flux_3d performs: the same bits.  Each group's
-// results are kept in program order (keep_order): without that a
-// single-orientation plane task at 11 binary64 fields spilled 248 VGPRs,
-// with it it took 300 and spilled none.
+// results are kept in program order (keep_order), and every point's flux goes
+// into its running sum before the next point's states are formed.
+//
+// What bounds it in binary64 are the waits for its about 11,800 stencil loads
+// a leaf, mostly served by L2 (the tile is 242 KB at 11 fields): with one
+// wavefront a SIMD (384 registers) nothing covers them.  At 256 registers,
+// which the passes of the column and the running sums allow (34 spilled, in
+// the column, at 11 fields, none up to 8), two do.  A substep of 3,100 leaves,
+// ms, with the fill: 3.35 and 2.67 (6 fields), 4.79 and 3.56 (8), 6.77 and 4.94
+// (11).  binary32 ran two a SIMD before and is bound by its instructions: it
+// gains from the running sums alone (1.22 and 1.14 ms, 6 fields; 2.13 and
+// 2.12, 11) and loses 4 % with the column in passes; three wavefronts a SIMD
+// (workgroups of 6) lost 10 %.
 // ---------------------------------------------------------------------------
 
 // The flux store of k_step3d_ws: k_step3d_wg's 27 planes and a spare one
@@ -574,18 +603,6 @@ constexpr size_t ws3d_lds_bytes() {
 // the centre point, a line of its own.
 constexpr int WS_PA[5] = {1, 1, 0, 1, 0};
 constexpr int WS_PB[5] = {1, -1, 1, 0, 0};
-
-// Running Simpson sums of one field over the pairs: pair 0 gives
-// (h(-1,-1) + h(1,1)), pair 1 adds (h(1,-1) + h(-1,1)) for the corners,
-// pairs 2 and 3 do the same for the edges, the centre closes the sum.
-template <typename T>
-__device__ __forceinline__ void simpson_pair(int p, T hp, T hm, T& sa, T& sb, T& out) {
-  if (p == 0) sa = hm + hp;
-  else if (p == 1) sa = sa + (hp + hm);
-  else if (p == 2) sb = hm + hp;
-  else if (p == 3) sb = sb + (hm + hp);
-  else out = simpson_close(sa, sb, hp);
-}
 
 // Value of the previous cell along D within the lane's cell plane, lane
 // (x, y) = x + 8 y: for x, lane - 1 by a DPP row shift (the lanes without a
@@ -645,42 +662,47 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
     constexpr int s0 = SX + SY + SZ, s1 = SX - SY - SZ, s2 = SX + SY - SZ, s3 = SX - SY + SZ;
     T vl[8], vr[8], ha[8];  // points: x (1,1) (-1,-1) (1,-1) (-1,1), y the same
     {
-      T xL[4][NF_CORE], xR[4][NF_CORE], yL[4][NF_CORE], yR[4][NF_CORE];
+      T lo[4][NF_CORE], hi[4][NF_CORE];
 #pragma unroll
       for (int f = 0; f < NF_CORE; ++f) {
-        T l0, h0, l1, h1, l2, h2, l3, h3;
         const T* q = Gt + f * fsG + t;
-        parabola(q, s0, l0, h0);
-        parabola(q, s1, l1, h1);
-        parabola(q, s2, l2, h2);
-        parabola(q, s3, l3, h3);
-        xL[0][f] = prev_cell<0>(h0); xR[0][f] = l1;  // x (1,1)
-        xL[1][f] = prev_cell<0>(h1); xR[1][f] = l0;  // x (-1,-1)
-        xL[2][f] = prev_cell<0>(h2); xR[2][f] = l3;  // x (1,-1)
-        xL[3][f] = prev_cell<0>(h3); xR[3][f] = l2;  // x (-1,1)
-        yL[0][f] = prev_cell<1>(h0); yR[0][f] = h3;  // y (1,1)
-        yL[1][f] = prev_cell<1>(l3); yR[1][f] = l0;  // y (-1,-1)
-        yL[2][f] = prev_cell<1>(h2); yR[2][f] = h1;  // y (1,-1)
-        yL[3][f] = prev_cell<1>(l1); yR[3][f] = l2;  // y (-1,1)
-      }
-      T hx[4][NF_CORE], hy[4][NF_CORE];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        core_flux(ph, 0, xL[q], xR[q], hx[q], vl[q], vr[q], ha[q], bx);
-        core_flux(ph, 1, yL[q], yR[q], hy[q], vl[4 + q], vr[4 + q], ha[4 + q], by);
+        parabola(q, s0, lo[0][f], hi[0][f]);
+        parabola(q, s1, lo[1][f], hi[1][f]);
+        parabola(q, s2, lo[2][f], hi[2][f]);
+        parabola(q, s3, lo[3][f], hi[3][f]);
       }
 #pragma unroll
-      for (int f = 0; f < NF_CORE; ++f) {
-        acc[f].xc = (hx[1][f] + hx[0][f]) + (hx[2][f] + hx[3][f]);
-        acc[f].yc = (hy[1][f] + hy[0][f]) + (hy[2][f] + hy[3][f]);
-        keep_order(acc[f].xc);
-        keep_order(acc[f].yc);
-      }
+      for (int q = 0; q < 8; q += 2) {
+        T h[2][NF_CORE];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        keep_order(vl[q]);
-        keep_order(vr[q]);
-        keep_order(ha[q]);
+        for (int i = 0; i < 2; ++i) {
+          T L[NF_CORE], R[NF_CORE];
+#pragma unroll
+          for (int f = 0; f < NF_CORE; ++f) {
+            switch (q + i) {
+              case 0: L[f] = prev_cell<0>(hi[0][f]); R[f] = lo[1][f]; break;  // x (1,1)
+              case 1: L[f] = prev_cell<0>(hi[1][f]); R[f] = lo[0][f]; break;  // x (-1,-1)
+              case 2: L[f] = prev_cell<0>(hi[2][f]); R[f] = lo[3][f]; break;  // x (1,-1)
+              case 3: L[f] = prev_cell<0>(hi[3][f]); R[f] = lo[2][f]; break;  // x (-1,1)
+              case 4: L[f] = prev_cell<1>(hi[0][f]); R[f] = hi[3][f]; break;  // y (1,1)
+              case 5: L[f] = prev_cell<1>(lo[3][f]); R[f] = lo[0][f]; break;  // y (-1,-1)
+              case 6: L[f] = prev_cell<1>(hi[2][f]); R[f] = hi[1][f]; break;  // y (1,-1)
+              default: L[f] = prev_cell<1>(lo[1][f]); R[f] = lo[2][f]; break;  // y (-1,1)
+            }
+          }
+          core_flux(ph, q >= 4, L, R, h[i], vl[q + i], vr[q + i], ha[q + i], q < 4 ? bx : by);
+#pragma unroll
+          for (int f = 0; f < NF_CORE; ++f) keep_order(h[i][f]);
+          keep_order(vl[q + i]);
+          keep_order(vr[q + i]);
+          keep_order(ha[q + i]);
+        }
+#pragma unroll
+        for (int f = 0; f < NF_CORE; ++f) {
+          T& c = q < 4 ? acc[f].xc : acc[f].yc;
+          c = (q & 2) == 0 ? h[1][f] + h[0][f] : c + (h[0][f] + h[1][f]);
+          keep_order(c);
+        }
       }
     }
 #pragma unroll
@@ -718,48 +740,43 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
     constexpr int NP = 4;
     T vl[NP], vr[NP], ha[NP];
     {
-      T L[NP][NF_CORE], R[NP][NF_CORE];
+      T lA[NF_CORE], hA[NF_CORE], lB[NF_CORE], hB[NF_CORE];
 #pragma unroll
       for (int f = 0; f < NF_CORE; ++f) {
-        T lA, hA, lB, hB;
         const T* q = Gt + f * fsG + t;
-        parabola(q, sA, lA, hA);
-        parabola(q, sB, lB, hB);
-        if (G == 0) {
-          L[0][f] = prev_cell<0>(hB); R[0][f] = lA;
-          L[1][f] = prev_cell<0>(hA); R[1][f] = lB;
-        } else if (G == 1) {
-          L[0][f] = prev_cell<1>(hB); R[0][f] = lA;
-          L[1][f] = prev_cell<1>(hA); R[1][f] = lB;
-        } else {
-          L[0][f] = prev_cell<0>(hB); R[0][f] = lA;
-          L[1][f] = prev_cell<0>(hA); R[1][f] = lB;
-          L[2][f] = prev_cell<1>(lB); R[2][f] = lA;
-          L[3][f] = prev_cell<1>(hA); R[3][f] = hB;
+        parabola(q, sA, lA[f], hA[f]);
+        parabola(q, sB, lB[f], hB[f]);
+      }
+#pragma unroll
+      for (int q = 0; q < (G == 2 ? 4 : 2); q += 2) {
+        T h[2][NF_CORE];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int D = G == 0 ? 0 : (G == 1 ? 1 : (q < 2 ? 0 : 1));
+          T L[NF_CORE], R[NF_CORE];
+#pragma unroll
+          for (int f = 0; f < NF_CORE; ++f) {
+            if (D == 0) {
+              L[f] = prev_cell<0>(i == 0 ? hB[f] : hA[f]);
+              R[f] = i == 0 ? lA[f] : lB[f];
+            } else {
+              L[f] = prev_cell<1>(i == 0 ? (G == 1 ? hB[f] : lB[f]) : hA[f]);
+              R[f] = i == 0 ? lA[f] : (G == 1 ? lB[f] : hB[f]);
+            }
+          }
+          core_flux(ph, D, L, R, h[i], vl[q + i], vr[q + i], ha[q + i], D == 0 ? bx : by);
+#pragma unroll
+          for (int f = 0; f < NF_CORE; ++f) keep_order(h[i][f]);
+          keep_order(vl[q + i]);
+          keep_order(vr[q + i]);
+          keep_order(ha[q + i]);
         }
-      }
-      T h[NP][NF_CORE];
 #pragma unroll
-      for (int q = 0; q < (G == 2 ? 4 : 2); ++q) {
-        const int D = G == 0 ? 0 : (G == 1 ? 1 : (q < 2 ? 0 : 1));
-        core_flux(ph, D, L[q], R[q], h[q], vl[q], vr[q], ha[q], D == 0 ? bx : by);
-      }
-#pragma unroll
-      for (int f = 0; f < NF_CORE; ++f) {
-        if (G == 0) acc[f].xe = h[0][f] + h[1][f];
-        else if (G == 1) acc[f].ye = h[0][f] + h[1][f];
-        else {
-          acc[f].xe = acc[f].xe + (h[0][f] + h[1][f]);
-          acc[f].ye = acc[f].ye + (h[2][f] + h[3][f]);
+        for (int f = 0; f < NF_CORE; ++f) {
+          T& e = G == 0 || (G == 2 && q == 0) ? acc[f].xe : acc[f].ye;
+          e = G < 2 ? h[0][f] + h[1][f] : e + (h[0][f] + h[1][f]);
+          keep_order(e);
         }
-        keep_order(acc[f].xe);
-        keep_order(acc[f].ye);
-      }
-#pragma unroll
-      for (int q = 0; q < (G == 2 ? 4 : 2); ++q) {
-        keep_order(vl[q]);
-        keep_order(vr[q]);
-        keep_order(ha[q]);
       }
     }
 #pragma unroll
@@ -861,11 +878,143 @@ __device__ __forceinline__ void ws_boundary(const GridArgs& g, const Phys<T>& ph
   }
 }
 
-// Column task: z-faces c0..c1 of lane (x, y)'s column into Hs, in the
-// field order of the plane task.  The cell below face c0 only fills the
-// carry.
+// One pass of the column task over z-faces c0..c1: the point pairs P0 .. P0 +
+// NP - 1.  Carries the right ends of those pairs' lines in the cell below and
+// keeps the faces' running Simpson sums in their slots of the flux store.
+template <typename T, int NF, int P0, int NP>
+__device__ __forceinline__ void ws_column_pass(const GridArgs& g, const Phys<T>& ph,
+                                               const T* __restrict__ Gt, size_t fsG, int leaf,
+                                               int c0, int c1, int lane,
+                                               T (&Hs)[WS_PLANES][NF][64], bool& bad) {
+  constexpr int SU = 1, SV = TW, SD = TW * TW;
+  constexpr int NQ = P0 < 4 ? 2 : 1;  // points and lines of a pair
+  const int x = lane & 7, y = lane >> 3;
+  T cr[NP * NQ][NF];  // [NQ p] line e(a, b), [NQ p + 1] line e(-a, -b)
+  {
+    const T* t = Gt + tile_at(x, y, c0 - 1);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const int o = WS_PA[P0 + p] * SU + WS_PB[P0 + p] * SV;
+        cr[NQ * p][f] = line_end(t + f * fsG, SD + o, true);
+        keep_order(cr[NQ * p][f]);
+        if (NQ == 2) {
+          cr[NQ * p + NQ - 1][f] = line_end(t + f * fsG, SD - o, true);
+          keep_order(cr[NQ * p + NQ - 1][f]);
+        }
+      }
+    }
+  }
+#pragma unroll 1
+  for (int c = c0; c <= c1; ++c) {
+    const T* t = Gt + tile_at(x, y, c);
+    T vl[NP * NQ], vr[NP * NQ], ha[NP * NQ], sum[NF];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int o = WS_PA[P0 + p] * SU + WS_PB[P0 + p] * SV;
+      T lA[NF_CORE], rA[NF_CORE], lB[NF_CORE], rB[NF_CORE], h[2][NF_CORE];
+#pragma unroll
+      for (int f = 0; f < NF_CORE; ++f) {
+        parabola(t + f * fsG, SD + o, lA[f], rA[f]);
+        if (NQ == 2) parabola(t + f * fsG, SD - o, lB[f], rB[f]);
+      }
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) {
+        const int q = NQ * p + i;
+        T L[NF_CORE], R[NF_CORE];
+#pragma unroll
+        for (int f = 0; f < NF_CORE; ++f) {
+          L[f] = cr[q][f];
+          R[f] = NQ == 2 && i == 0 ? lB[f] : lA[f];
+        }
+        core_flux(ph, 2, L, R, h[i], vl[q], vr[q], ha[q], bad);
+#pragma unroll
+        for (int f = 0; f < NF_CORE; ++f) {
+          cr[q][f] = i == 0 ? rA[f] : rB[f];
+          keep_order(h[i][f]);
+          keep_order(cr[q][f]);
+        }
+        keep_order(vl[q]);
+        keep_order(vr[q]);
+        keep_order(ha[q]);
+      }
+#pragma unroll
+      for (int f = 0; f < NF_CORE; ++f) {
+        if (P0 == 4) sum[f] = h[0][f];
+        else if (P0 == 0 || (P0 == 2 && p == 0)) sum[f] = h[1][f] + h[0][f];
+        else if (P0 == 1) sum[f] = h[0][f] + h[1][f];
+        else sum[f] = sum[f] + (h[1][f] + h[0][f]);
+        keep_order(sum[f]);
+      }
+    }
+#pragma unroll
+    for (int f = NF_CORE; f < NF; ++f) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const int o = WS_PA[P0 + p] * SU + WS_PB[P0 + p] * SV;
+        T lA, rA, lB = T(0), rB = T(0), h[2] = {T(0), T(0)};
+        parabola(t + f * fsG, SD + o, lA, rA);
+        if (NQ == 2) parabola(t + f * fsG, SD - o, lB, rB);
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+          const int q = NQ * p + i;
+          h[i] = passive_flux(cr[q][f], NQ == 2 && i == 0 ? lB : lA, vl[q], vr[q], ha[q]);
+          cr[q][f] = i == 0 ? rA : rB;
+          keep_order(cr[q][f]);
+        }
+        if (P0 == 4) sum[f] = h[0];
+        else if (P0 == 0 || (P0 == 2 && p == 0)) sum[f] = h[1] + h[0];
+        else if (P0 == 1) sum[f] = h[0] + h[1];
+        else sum[f] = sum[f] + (h[1] + h[0]);
+      }
+      keep_order(sum[f]);
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      T& slot = Hs[18 + c][f][lane];
+      if (P0 == 0) slot = sum[f];
+      else if (P0 == 1) slot = slot + sum[f];
+      else if (P0 == 2) slot = simpson_edges(slot, sum[f]);
+      else slot = sum[f] = simpson_centre(slot, sum[f]);
+    }
+    if (P0 == 4 && g.reg && (c == 0 || c == SUB))
+      record_faces<T, NF, 0, NF>(g, leaf, 2, c, x, y, sum);
+  }
+}
+
+// Column task of binary64: z-faces c0..c1 of lane (x, y)'s column into Hs, by
+// passes over the corner pairs, the edge pairs together and the centre.  A
+// pass carries at most 4 lines' ends instead of 9 (99 values at 11 fields),
+// and the Simpson sums wait in the flux store.  The cell below face c0 only
+// fills the carry.
 template <typename T, int NF>
 __device__ __forceinline__ void ws_column(const GridArgs& g, const Phys<T>& ph,
+                                          const T* __restrict__ Gt, size_t fsG, int leaf, int c0,
+                                          int c1, int lane, T (&Hs)[WS_PLANES][NF][64],
+                                          bool& bad) {
+  ws_column_pass<T, NF, 0, 1>(g, ph, Gt, fsG, leaf, c0, c1, lane, Hs, bad);
+  ws_column_pass<T, NF, 1, 1>(g, ph, Gt, fsG, leaf, c0, c1, lane, Hs, bad);
+  ws_column_pass<T, NF, 2, 2>(g, ph, Gt, fsG, leaf, c0, c1, lane, Hs, bad);
+  ws_column_pass<T, NF, 4, 1>(g, ph, Gt, fsG, leaf, c0, c1, lane, Hs, bad);
+}
+
+// Running Simpson sums of one field over the pairs: pair 0 gives
+// (h(-1,-1) + h(1,1)), pair 1 adds (h(1,-1) + h(-1,1)) for the corners,
+// pairs 2 and 3 do the same for the edges, the centre closes the sum.
+template <typename T>
+__device__ __forceinline__ void simpson_pair(int p, T hp, T hm, T& sa, T& sb, T& out) {
+  if (p == 0) sa = hm + hp;
+  else if (p == 1) sa = sa + (hp + hm);
+  else if (p == 2) sb = hm + hp;
+  else if (p == 3) sb = sb + (hm + hp);
+  else out = simpson_close(sa, sb, hp);
+}
+
+// Column task of binary32: the same in one sweep over the faces, carrying all
+// 9 lines' ends.
+template <typename T, int NF>
+__device__ __forceinline__ void ws_column_carry(const GridArgs& g, const Phys<T>& ph,
                                           const T* __restrict__ Gt, size_t fsG, int leaf, int c0,
                                           int c1, int lane, T (&Hs)[WS_PLANES][NF][64],
                                           bool& bad) {
@@ -973,22 +1122,31 @@ __device__ __forceinline__ void ws_column(const GridArgs& g, const Phys<T>& ph,
   }
 }
 
-// Work of each wavefront, in this order (the boundary faces, which span the
-// whole tile, come last; by VALU instructions at 11 binary64 fields the
-// lists are 68 k, 58 k, 69 k and 70 k, and no other split of these tasks
-// does better):
-//   0: z-faces 4..8, y-face 8
-//   1: z-faces 0..3, plane 7
-//   2: planes 0..3, x-face 8
-//   3: planes 4..6, x-face 0, y-face 0
-// written out per wavefront, not as a list of tasks in one loop: in a loop
-// the compiler keeps every task's loop-invariant values in registers
-// through all of them.
-// binary32 at two workgroups per CU where two flux stores fit in LDS (256
-// registers; the store is 77 KB at 11 fields), binary64 at one.
+// Work of each wavefront, in this order.  binary64, 8 wavefronts, of which w
+// and w + 4 share a SIMD; in thousands of VALU instructions at 11 fields a
+// plane is 13.7, a boundary face 14.5 and a column 6.4 and 9.3 a face, so the
+// SIMDs get 77, 67, 68 and 68:
+//   0: z-faces 6..8                    4: planes 0 and 4, x-face 8
+//   1: z-faces 0 and 1, x-face 0       5: planes 1 and 5
+//   2: z-faces 2 and 3, y-face 0       6: planes 2 and 6
+//   3: z-faces 4 and 5, y-face 8       7: planes 3 and 7
+// Planes are interleaved so that those worked on at once share tile planes
+// (runs of planes to each: 5.14 ms instead of 5.08; z-faces by threes: 5.11
+// and 4.94; the planes and faces drawn from a counter in LDS: 5.02, but 3 %
+// slower at 6 and 8 fields).  binary32, 4 wavefronts:
+//   0: z-faces 4..8, y-face 8          2: planes 0..3, x-face 8
+//   1: z-faces 0..3, plane 7           3: planes 4..6, x-face 0, y-face 0
+// The boundary faces, which span the whole tile, come last; before the
+// columns they cost 2 %.
+// binary32 runs two workgroups per CU where two flux stores fit in LDS (the
+// store is 77 KB at 11 fields), binary64 one (154 KB).
 template <typename T, int NF>
-__global__ void __launch_bounds__(256, (sizeof(T) == 4 && 2 * ws3d_lds_bytes<T, NF>() <= 160 * 1024)
-                                           ? 2 : 1)
+constexpr int ws_waves() {
+  return sizeof(T) == 8 ? 8 : 4;
+}
+template <typename T, int NF>
+__global__ void __launch_bounds__((64 * ws_waves<T, NF>()),
+                                  (sizeof(T) == 8 || 2 * ws3d_lds_bytes<T, NF>() <= 160 * 1024 ? 2 : 1))
     k_step3d_ws(StepArgs s, const T* __restrict__ G) {
   __shared__ T Hs[WS_PLANES][NF][64];  // the layout of k_step3d_wg and a spare plane
   const GridArgs& g = s.g;
@@ -1004,20 +1162,33 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 && 2 * ws3d_lds_bytes<T, 
   const size_t fsG = (size_t)g.n_leaves * TILE;
   const T* __restrict__ Gt = G + (size_t)leaf * TILE;
   bool bad = false;
-  if (wave < 2)
-    ws_column<T, NF>(g, ph, Gt, fsG, leaf, wave == 0 ? 4 : 0, wave == 0 ? SUB : 3, lane, Hs, bad);
-  const int z0 = wave == 1 ? 7 : (wave == 2 ? 0 : 4);
-  const int z1 = wave == 0 ? -1 : (wave == 1 ? 7 : (wave == 2 ? 3 : 6));
+  int c0, c1, z0, z1, k0, k1;  // z-faces, planes and boundary tasks k0, k0 + 2, .. k1
+  if constexpr (ws_waves<T, NF>() == 8) {
+    c0 = wave < 4 ? (wave == 0 ? 6 : 2 * wave - 2) : 1;
+    c1 = wave < 4 ? (wave == 0 ? SUB : 2 * wave - 1) : 0;
+    z0 = wave < 4 ? 0 : wave - 4;
+    z1 = wave < 4 ? -1 : 7;
+    k0 = wave == 4 ? 1 : (wave == 1 ? 0 : wave);
+    k1 = wave == 0 || wave > 4 ? -1 : k0;
+  } else {
+    c0 = wave == 0 ? 4 : (wave == 1 ? 0 : 1);
+    c1 = wave == 0 ? SUB : (wave == 1 ? 3 : 0);
+    z0 = wave == 1 ? 7 : (wave == 2 ? 0 : 4);
+    z1 = wave == 0 ? -1 : (wave == 1 ? 7 : (wave == 2 ? 3 : 6));
+    k0 = wave == 0 ? 3 : (wave == 3 ? 0 : 1);
+    k1 = wave == 0 ? 3 : (wave == 1 ? 0 : (wave == 2 ? 1 : 2));
+  }
+  if (c0 <= c1) {
+    if constexpr (sizeof(T) == 8) ws_column<T, NF>(g, ph, Gt, fsG, leaf, c0, c1, lane, Hs, bad);
+    else ws_column_carry<T, NF>(g, ph, Gt, fsG, leaf, c0, c1, lane, Hs, bad);
+  }
 #pragma unroll 1
-  for (int z = z0; z <= z1; ++z) ws_plane_xy<T, NF>(ph, Gt, fsG, z, lane, Hs, bad);
-  // boundary tasks k0, k0 + 2, ... up to k1
-  const int k0 = wave == 0 ? 3 : (wave == 3 ? 0 : 1);
-  const int k1 = wave == 0 ? 3 : (wave == 1 ? 0 : (wave == 2 ? 1 : 2));
+  for (int z = z0; z <= z1; z += ws_waves<T, NF>() == 8 ? 4 : 1) ws_plane_xy<T, NF>(ph, Gt, fsG, z, lane, Hs, bad);
 #pragma unroll 1
   for (int k = k0; k <= k1; k += 2) ws_boundary<T, NF>(g, ph, Gt, fsG, leaf, k, lane, Hs, bad);
   if (g.status && __any(bad) && lane == 0) atomicOr(g.status, (int)HYDRO_STATUS_UNPHYSICAL);
   __syncthreads();
-  finish_leaf_3d<T, NF, WS_PLANES>(s, Hs, leaf, c4);
+  finish_leaf_3d<T, NF, 64 * ws_waves<T, NF>(), WS_PLANES>(s, Hs, leaf, c4);
 }
 
 // Launch of the 3D step: where the workgroup forms' flux store fits in LDS
@@ -1033,7 +1204,7 @@ hipError_t launch_step3d_one(const StepArgs& a, int blocks, const T* G, int wg, 
   }
   if constexpr (ws3d_lds_bytes<T, NF>() <= 160 * 1024) {
     if (wg == 2) {
-      hipLaunchKernelGGL((k_step3d_ws<T, NF>), dim3(blocks), dim3(256), 0, st, a, G);
+      hipLaunchKernelGGL((k_step3d_ws<T, NF>), dim3(blocks), dim3((64 * ws_waves<T, NF>())), 0, st, a, G);
       return hipGetLastError();
     }
   }

@@ -296,3 +296,31 @@ def test_ghost_fill_at_any_alignment(env, shift, nf, dtype):
         assert torch.equal(plain, G)
     rest = torch.cat([buf[:shift], buf[shift + n:]])
     assert torch.all(rest == -7.0)
+
+
+@pytest.mark.parametrize("dtype,nf", [(0, 7), (0, 8), (0, 9), (0, 10), (1, 6), (1, 8), (1, 12)])
+def test_3d_forms_at_every_register_layout(env, dtype, nf):
+    """The workgroup form of the 3D step that shares line reconstructions (8
+    wavefronts in binary64, 4 in binary32) at the field counts between the
+    smallest and the largest it takes: the bits of the one-wavefront form,
+    with the flux correction and rotation on."""
+    torch, hb = env
+    print(f"case 3D forms dtype {dtype} nf {nf}", flush=True)
+    w = inputs.blobs(base=2, max_level=2, threshold=0.5)
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    U = torch.from_numpy(_species(w, nf, nf)).to("cuda").to(tdt).contiguous()
+    grid = hb.Grid(w.leaf_coord, w.base, nf, dtype, omega=0.7, reflux=True,
+                   reconstruction=hb.HYDRO_RECON_3D)
+    old = hb.hydro_get_option(dtype, nf, hb.HYDRO_OPT_3D_WORKGROUP)
+    outs = []
+    try:
+        for form in (2, 0):
+            hb.hydro_set_option(dtype, nf, hb.HYDRO_OPT_3D_WORKGROUP, form)
+            W1, W2, Un = (grid.empty_state() for _ in range(3))
+            dt = torch.zeros(1, dtype=torch.float64, device="cuda")
+            hb.hydro_rk3_step(grid, U, W1, W2, Un, 0.4, dt)
+            assert hb.hydro_check_status(grid) == hb.HYDRO_OK
+            outs.append(Un.cpu().numpy())
+    finally:
+        hb.hydro_set_option(dtype, nf, hb.HYDRO_OPT_3D_WORKGROUP, old)
+    assert np.array_equal(outs[0], outs[1])
