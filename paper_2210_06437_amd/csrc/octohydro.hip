@@ -563,13 +563,15 @@ struct Options {
 // (binary32, 9 fields, 1000 leaves: 41, 42, 37).
 // Up to the field count whose state fits 256 registers with few spills one
 // wavefront holds all fields; beyond it the second wavefront's barrier each
-// step costs less than the spills or the lower occupancy.  6 binary64 and all
-// binary32 counts need no cap: they stay below 256 registers by themselves.
+// step costs less than the spills or the lower occupancy.  6 binary64 fields
+// stay just below 256 registers by themselves (241, with the CFL minimum 255;
+// at 257, one wavefront per SIMD, the chained step of 4096 leaves took 466 us
+// instead of 432) and all binary32 counts well below.
 static Options default_options(int dtype, int nf) {
   Options o;
   if (dtype == HYDRO_F64) {
     o.waves_per_leaf = nf >= 10 ? 2 : 1;
-    o.waves_per_simd = (nf >= 7 && nf <= 9) || nf >= 15 ? 2 : 1;
+    o.waves_per_simd = nf <= 9 || nf >= 15 ? 2 : 1;
   } else {
     o.waves_per_leaf = nf >= 9 ? 2 : 1;
   }

@@ -485,22 +485,27 @@ __device__ __forceinline__ void restrict_out(const StepArgs& s, double* __restri
   }
 }
 
-// Per-cell CFL quantity dx / (max(|v_x|, |v_y|, |v_z|) + c) of a stored
-// state (rho, s, E, tau as stored, in binary64), evaluated operation by
-// operation as the time-step pass hydro_cfl_dt does.
+// Signal speed max(|v_x|, |v_y|, |v_z|) + c of a stored state (rho, s, E, tau
+// as stored, in binary64): the bits of the time-step pass hydro_cfl_dt.  Where
+// rho and c^2 lie in the range of the refined reciprocal and root (see EosPair)
+// these take the place of IEEE division and root.
 template <typename T>
-__device__ __forceinline__ double cfl_quantity(const GridArgs& g, const T (&cv)[NF_CORE],
-                                               double dx) {
+__device__ __forceinline__ double cfl_speed(const GridArgs& g, const T (&cv)[NF_CORE]) {
   const double rho = (double)cv[0], sx = (double)cv[1], sy = (double)cv[2];
   const double sz = (double)cv[3], E = (double)cv[4];
-  const double rinv = 1.0 / rho;
   const double ss = (sx * sx + sy * sy) + sz * sz;
-  double ei = E - 0.5 * ss * rinv;
-  if (ei < g.eta1 * E) ei = tau_energy((double)cv[5], g.gamma);
-  const double p = (g.gamma - 1.0) * ei;
-  const double c = sqrt(g.gamma * p * rinv);
-  const double vmax = fmax(fmax(fabs(sx * rinv), fabs(sy * rinv)), fabs(sz * rinv));
-  return dx / (vmax + c);
+  double rinv = recip_refined(rho);
+  double ei = fma(-0.5, ss * rinv, E);  // the halving is exact
+  double x = g.gamma * ((g.gamma - 1.0) * ei) * rinv;
+  double c = sqrt_refined(x);
+  if (max(range_key(rho), range_key(x)) > FAST_SPAN<double> || ei < g.eta1 * E) {
+    rinv = 1.0 / rho;
+    ei = E - 0.5 * ss * rinv;
+    if (ei < g.eta1 * E) ei = tau_energy((double)cv[5], g.gamma);
+    x = g.gamma * ((g.gamma - 1.0) * ei) * rinv;
+    c = sqrt(x);
+  }
+  return fmax(fmax(fabs(sx * rinv), fabs(sy * rinv)), fabs(sz * rinv)) + c;
 }
 
 __device__ __forceinline__ double wave_min(double v) {
@@ -509,13 +514,24 @@ __device__ __forceinline__ double wave_min(double v) {
   return v;
 }
 
-// Wavefront minimum of a positive binary64 into *out by an unsigned 64-bit
-// atomic min on its bit pattern (positive doubles order like their bits).
-__device__ __forceinline__ void atomic_min_positive(double* out, double v, int lane) {
-  v = wave_min(v);
-  if (lane == 0)
-    atomicMin(reinterpret_cast<unsigned long long*>(out),
-              (unsigned long long)__double_as_longlong(v));
+// The CFL minimum of a wavefront's cells, all of one leaf, into *out from each
+// lane's largest signal speed.  Division rounds monotonically, so the least
+// dx / speed is dx by the largest speed: one division a wavefront instead of
+// one a cell.  A speed that is not a number leaves no trace, as in fmin.  By an
+// unsigned 64-bit atomic min (positive doubles order like their bits), left out
+// where the stored minimum is already as small: all wavefronts of the grid meet
+// at this one address.  The load may be late, which costs an atomic at most.
+// Chained step of 8,000 leaves at 6 fields, us, without and with the load: 831
+// and 819 (binary64), 478 and 467 (binary32).
+__device__ __forceinline__ void cfl_minimum(double* out, double speed, double inv_dx, int lane) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) speed = fmax(speed, __shfl_xor(speed, o, 64));
+  if (lane == 0) {
+    const double q = (1.0 / inv_dx) / speed;
+    unsigned long long* o = reinterpret_cast<unsigned long long*>(out);
+    const unsigned long long b = (unsigned long long)__double_as_longlong(q);
+    if (b < __hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(o, b);
+  }
 }
 
 // The lane number as a value the compiler knows nothing about, so that what a
@@ -1033,7 +1049,7 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
 template <typename T, int NF, int MODE, int ZU, int AP>
 __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, const LeafInfo& li,
                                         double* __restrict__ acc, int h, int lane, double dt, double inv_dx, bool& bad,
-                                        double& cflmin, int lnode) {
+                                        double& speed, int lnode) {
   const GridArgs& g = s.g;
   const size_t fs = (size_t)g.n_leaves * CELLS;
   const uint32_t fs_b = (uint32_t)(fs * sizeof(T));
@@ -1100,7 +1116,7 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
             restrict_out<T, L::PLANE>(s, &acc[f * L::HALF + ai], lnode, f, x, y, i, o);
         }
       }
-      if constexpr (MODE == STEP_CFL) cflmin = fmin(cflmin, cfl_quantity<T>(g, cv, 1.0 / inv_dx));
+      if constexpr (MODE == STEP_CFL) speed = fmax(speed, cfl_speed<T>(g, cv));
     }
 #pragma unroll
     for (int f = 0; f < NF; ++f) Hprev[f] = (double)H[f];
@@ -1111,9 +1127,17 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
 // MODE: STEP_PLAIN, STEP_RESTRICT (s.node_out set: the node copies of the
 // output are left as well) or STEP_CFL (s.dt_next set: the CFL minimum of
 // the output is taken as well); separate kernels, so that each keeps only
-// the registers its own work needs.
+// the registers its own work needs.  The binary32 kernels that run three
+// wavefronts per SIMD by themselves (up to 155 registers) keep to 168 with the
+// CFL minimum too, where they would take 172: chained step of 65,535 leaves at
+// 11 fields (k_step2) 6.43 ms without and 6.08 with the bound.
 template <typename T, int NF, int W, int MODE>
-__global__ void __launch_bounds__(64, W) k_step(StepArgs s) {
+constexpr int step_waves() {
+  return sizeof(T) == 4 && NF <= 13 && MODE == STEP_CFL ? 3 : W;
+}
+template <typename T, int NF, int W, int MODE>
+__global__ void __launch_bounds__(64, (NF == NF_CORE ? step_waves<T, NF, W, MODE>() : W))
+    k_step(StepArgs s) {
   constexpr int AP = W == 2 ? 8 : 9;  // accumulator row pitch (see AccLayout)
   // Unroll factors of the stream loops of phases XY and Z (9 and 5 are whole).
   // Unrolled, the recurrence moves to other registers instead of being copied
@@ -1142,17 +1166,17 @@ __global__ void __launch_bounds__(64, W) k_step(StepArgs s) {
   ph.eta1 = (T)g.eta1;
 
   bool bad = false;
-  double cflmin = INFINITY;
+  double speed = 0.0;  // largest of the lane's cells (CFL)
   const int lnode = MODE == STEP_RESTRICT ? g.leaf_node[leaf] : -1;
 #pragma unroll 1
   for (int h = 0; h < 2; ++h) {
     phase_xy<T, NF, XU, AP>(s, ph, li, acc, h, fresh(lane), bad);
     wave_lds_sync();
     phase_z<T, NF, MODE, ZU, AP>(s, ph, li, acc, h, fresh(lane), dt, inv_dx, bad,
-                                             cflmin, lnode);
+                                             speed, lnode);
     wave_lds_sync();
   }
-  if constexpr (MODE == STEP_CFL) atomic_min_positive(s.dt_next, cflmin, lane);
+  if constexpr (MODE == STEP_CFL) cfl_minimum(s.dt_next, speed, inv_dx, lane);
   if (g.status && __any(bad) && lane == 0) atomicOr(g.status, (int)HYDRO_STATUS_UNPHYSICAL);
 }
 
@@ -1324,7 +1348,7 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
                                               double* __restrict__ acc,
                                               SpeedSlot<T>* __restrict__ spd, int& sn, int h,
                                               int lane, double dt, double inv_dx, bool& bad,
-                                              double& cflmin, int lnode) {
+                                              double& speed, int lnode) {
   const GridArgs& g = s.g;
   const size_t fs = (size_t)g.n_leaves * CELLS;
   const uint32_t fs_b = (uint32_t)(fs * sizeof(T));
@@ -1392,7 +1416,7 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
         }
       }
       if constexpr (MODE == STEP_CFL && F0 == 0)
-        cflmin = fmin(cflmin, cfl_quantity<T>(g, cv, 1.0 / inv_dx));
+        speed = fmax(speed, cfl_speed<T>(g, cv));
     }
 #pragma unroll
     for (int f = 0; f < NG; ++f) Hprev[f] = (double)H[f];
@@ -1402,7 +1426,7 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
 // W = waves per SIMD the register budget allows (1: up to 512 VGPRs, 2: 256);
 // MODE as for k_step.
 template <typename T, int NF, int W, int MODE>
-__global__ void __launch_bounds__(128, W) k_step2(StepArgs s) {
+__global__ void __launch_bounds__(128, (step_waves<T, NF, W, MODE>())) k_step2(StepArgs s) {
   static_assert(NF > NF_CORE, "the second wavefront needs passive species");
   __shared__ __align__(16) double acc[NF * ACC_HALF];
   __shared__ SpeedSlot<T> spd[2];
@@ -1424,7 +1448,7 @@ __global__ void __launch_bounds__(128, W) k_step2(StepArgs s) {
   ph.eta1 = (T)g.eta1;
 
   bool bad = false;
-  double cflmin = INFINITY;
+  double speed = 0.0;  // largest of the lane's cells (CFL)
   const int lnode = MODE == STEP_RESTRICT ? g.leaf_node[leaf] : -1;
   int sn = 0;  // stream steps taken: selects the hand-off slot
   constexpr int NS = NF - NF_CORE;
@@ -1437,14 +1461,14 @@ __global__ void __launch_bounds__(128, W) k_step2(StepArgs s) {
     wave_lds_sync();
     if (wave == 0)
       phase_z_group<T, NF, 0, NF_CORE, MODE>(s, ph, li, acc, spd, sn, h, fresh(lane), dt, inv_dx,
-                                            bad, cflmin, lnode);
+                                            bad, speed, lnode);
     else
       phase_z_group<T, NF, NF_CORE, NS, MODE>(s, ph, li, acc, spd, sn, h, fresh(lane), dt, inv_dx,
-                                             bad, cflmin, lnode);
+                                             bad, speed, lnode);
     wave_lds_sync();
   }
   if constexpr (MODE == STEP_CFL) {
-    if (wave == 0) atomic_min_positive(s.dt_next, cflmin, lane);
+    if (wave == 0) cfl_minimum(s.dt_next, speed, inv_dx, lane);
   }
   if (g.status && __any(bad) && lane == 0) atomicOr(g.status, (int)HYDRO_STATUS_UNPHYSICAL);
 }
@@ -1561,7 +1585,7 @@ __global__ void __launch_bounds__(384, sizeof(T) == 4 && NF <= 8 ? 3 : 2) k_leaf
   const double dt = *s.dt;
   const double inv_dx = (double)(SUB * li.blocks);
   const int lnode = MODE == STEP_RESTRICT ? g.leaf_node[leaf] : -1;
-  double cflmin = INFINITY;
+  double speed = 0.0;  // largest of the lane's cells (CFL)
   const bool rot = g.omega != 0.0;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -1583,9 +1607,9 @@ __global__ void __launch_bounds__(384, sizeof(T) == 4 && NF <= 8 ? 3 : 2) k_leaf
           restrict_out<T, L::PLANE>(s, &at[f * L::FIELD], lnode, f, x, y, z, o);
       }
     }
-    if constexpr (MODE == STEP_CFL) cflmin = fmin(cflmin, cfl_quantity<T>(g, cv, 1.0 / inv_dx));
+    if constexpr (MODE == STEP_CFL) speed = fmax(speed, cfl_speed<T>(g, cv));
   }
-  if constexpr (MODE == STEP_CFL) atomic_min_positive(s.dt_next, cflmin, lane);
+  if constexpr (MODE == STEP_CFL) cfl_minimum(s.dt_next, speed, inv_dx, lane);
 }
 
 // Launch of k_leaf for any field count (units k_leaf_f64.hip, k_leaf_f32.hip).

@@ -324,3 +324,38 @@ def test_3d_forms_at_every_register_layout(env, dtype, nf):
     finally:
         hb.hydro_set_option(dtype, nf, hb.HYDRO_OPT_3D_WORKGROUP, old)
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("dtype,rho_exp,p_exp", [
+    (0, 0, 0), (0, -510, -510), (0, 0, -510), (0, 495, 10), (0, 0, -1030), (1, 0, 0),
+    (1, -30, 70), (1, 95, 0)])
+@pytest.mark.parametrize("n_leaves,nf", [(8, 6), (1000, 6), (1000, 11)])
+def test_cfl_minimum_left_by_the_step_is_that_of_a_pass(env, n_leaves, nf, dtype, rho_exp, p_exp):
+    """The minimum that the step kernel leaves beside its output, with the
+    refined reciprocal and root and one division per wavefront, has the bits
+    of the time-step pass over that output (IEEE operations, one division per
+    cell): densities and squared sound speeds inside and outside the refined
+    range, a quarter of the cells under the dual-energy switch."""
+    torch, hb = env
+    print(f"case {n_leaves} leaves nf {nf} dtype {dtype} rho 2^{rho_exp} p 2^{p_exp}", flush=True)
+    base, rng = round(n_leaves ** (1 / 3)), np.random.default_rng(9)
+    coord = inputs.uniform_leaves(base)
+    X, Y, Z = inputs.cell_centres(coord, base)
+    rho = 2.0 ** rho_exp * (1.0 + 0.1 * np.sin(2 * np.pi * X) + 1e-2 * rng.uniform(-1, 1, X.shape))
+    p = 2.0 ** p_exp * (1.0 + 0.1 * np.cos(2 * np.pi * Z) + 1e-2 * rng.uniform(-1, 1, X.shape))
+    zero = np.zeros_like(rho)
+    # a fast quarter of the box, whose kinetic energy hides the internal one
+    fast = np.where((X < 0.5) & (Y < 0.5), 100.0 * 2.0 ** (0.5 * (p_exp - rho_exp)), 0.0)
+    w = inputs.random_smooth(coord, base, nf=6, seed=nf)
+    w.U = inputs.conserved(rho, zero, zero, zero + fast, p)
+    U = _species(w, nf, nf) if nf > 6 else w.U
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    Ud = torch.from_numpy(U).to("cuda").to(tdt).contiguous()
+    grid = hb.Grid(coord, base, nf, dtype, cfl_epilogue=True)
+    W1, W2, out = (grid.empty_state() for _ in range(3))
+    dt, ref = (torch.zeros(2, dtype=torch.float64, device="cuda") for _ in range(2))
+    hb.hydro_cfl_dt(grid, Ud, 0.0, dt[1:])
+    hb.hydro_rk3_step(grid, Ud, W1, W2, out, 0.1, dt)
+    hb.hydro_cfl_dt(grid, out, 0.0, ref[1:])
+    got, want = dt[1].item(), ref[1].item()
+    assert got == want and got > 0.0, (got, want)
