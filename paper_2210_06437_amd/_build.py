@@ -1,8 +1,8 @@
 """Build liboctohydro.so in-tree with hipcc for gfx950.
 
 The library's translation units (host code and small kernels; the fused
-substep in binary64 and in binary32 storage; the 3D step, its instantiations
-spread over eight units; the table builder) are compiled to objects in
+substep in binary64 and in binary32 storage, with its form for small batches;
+the 3D step, its instantiations spread over eight units; the table builder) are compiled to objects in
 parallel and linked into one shared library.
 """
 from __future__ import annotations
@@ -26,9 +26,9 @@ SOURCES = sorted(glob.glob(os.path.join(CSRC, "*.hip"))) + [os.path.join(CSRC, "
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-# binary64 results must be reproducible operation by operation: no FMA
-# contraction, IEEE division and square root; packed FP32 instructions are
-# disabled for all device code.
+# binary64 results must have the bits of an operation-by-operation evaluation:
+# no FMA that the sources do not write, IEEE division and square root; packed
+# FP32 instructions are disabled for all device code.
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-ffp-contract=off", "-fno-fast-math",

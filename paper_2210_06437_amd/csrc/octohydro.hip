@@ -2,7 +2,7 @@
 // unit holds the C-ABI entry points, the host-side launch logic and the
 // small kernels; the method's device code and the step kernels are in
 // octohydro_kernels.h (the 3D step's in octohydro_kernels3d.h), instantiated
-// in the k_step_*.hip and k_step3d*.hip units.
+// in the k_step_*.hip, k_leaf_*.hip and k_step3d*.hip units.
 //
 // Kernels behind the C-ABI in include/octohydro.h:
 //   k_fill     ghost fill into materialised 14^3 tiles (hydro_fill_ghosts)
@@ -10,17 +10,20 @@
 //              (within an RK3 step the substeps leave them after the first)
 //   k_step     fused substep: neighbour gather + PPM + Kurganov-Tadmor flux +
 //              flux divergence + Runge-Kutta stage combination (hydro_step)
+//              (k_step2: two wavefronts a leaf; k_leaf: six, for small batches)
 //   k_step3d   the same with the full 3D reconstruction and face quadrature
+//              (k_step3d_wg and k_step3d_ws: a workgroup per leaf)
 //   k_reflux   coarse-fine flux correction
 //   k_cfl      global time step: per-cell dx / signal speed, wave64 min, one
 //              64-bit atomic min per workgroup (hydro_cfl_dt)
 //   k_totals   conserved totals with double-double accumulation
 //
 // The method (paper Sec. IV-C, V-B-1, VI; textbook forms named in the public
-// header) is evaluated operation by operation in the order the method states:
-// in binary64 every operation is one IEEE-754 operation rounded once, with no
-// FMA contraction, so the binary64 path reproduces a plain sequential
-// evaluation bit for bit.
+// header) is evaluated so that the binary64 path of the axis scheme and of the
+// 3D one reproduces a plain sequential evaluation, every operation rounded once,
+// bit for bit: an FMA stands only where its product is exact or inside a
+// division or root whose result is correctly rounded.  In binary32 products
+// and sums are fused and the recurrence carries differences, which rounds less.
 //
 // Layout in HBM: structure of arrays, field-major: U[f][leaf][z][y][x].
 // One 64-lane wavefront owns one leaf in k_step, in two z-halves: lanes

@@ -3,8 +3,9 @@
 // with their launchers.  Each kernel is instantiated only in the translation
 // unit that launches it (octohydro.hip: ghost fill, restriction, CFL, totals,
 // flux correction; k_step_f64.hip, k_step_f32.hip and their _cfl and
-// _restrict variants: the fused substep per precision and variant), so the
-// units compile in parallel.  The 3D step's device code is in
+// _restrict variants: the fused substep per precision and variant;
+// k_leaf_f64.hip, k_leaf_f32.hip: its form for small batches), so the units
+// compile in parallel.  The 3D step's device code is in
 // octohydro_kernels3d.h.
 #pragma once
 
@@ -887,13 +888,12 @@ constexpr int ACC_HALF = 4 * ACC_PLANE;
 
 // The same layout with row pitch AP (doubles).  AP = 9, the spare double per
 // row, puts the 8 lanes of an x-pencil group, which add into the same x of 8
-// rows, on distinct LDS banks; AP = 8 takes 11 % less LDS.  With the 256-
-// register budget the accumulator is what limits the workgroups per CU
-// (binary64 at 11 fields: 25.3 KB, 6 per CU; 22.5 KB with AP = 8, 7 per CU):
-// there AP = 8 made the binary32 substep of the 65,535-leaf case 8.5 % faster
-// (3.19 -> 2.92 ms); with the 512-register budget, where registers limit it
-// to 4 per CU, AP = 9 is 0.8 % faster.  The accumulator sums two exact
-// terms, so the layout does not change a bit of the result.
+// rows, on distinct LDS banks; AP = 8 takes 11 % less LDS, which decides the
+// workgroups of one wavefront per CU where registers do not (11 fields: 25.3 KB,
+// 6 per CU; 22.5 KB with AP = 8, 7 per CU).  k_step uses 8 with the 256-register
+// budget and 9 with the 512-register one, k_step2 and k_leaf use 9.  The
+// accumulator sums two exact terms, so the layout does not change a bit of
+// the result.
 template <int AP>
 struct AccLayout {
   static constexpr int PITCH = AP, PLANE = SUB * AP, HALF = 4 * SUB * AP;

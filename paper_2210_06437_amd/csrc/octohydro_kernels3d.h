@@ -575,16 +575,17 @@ __global__ void __launch_bounds__(256, 1) k_step3d_wg(StepArgs s, const T* __res
 // results are kept in program order (keep_order), and every point's flux goes
 // into its running sum before the next point's states are formed.
 //
-// What bounds it in binary64 are the waits for its about 11,800 stencil loads
-// a leaf, mostly served by L2 (the tile is 242 KB at 11 fields): with one
-// wavefront a SIMD (384 registers) nothing covers them.  At 256 registers,
-// which the passes of the column and the running sums allow (34 spilled, in
-// the column, at 11 fields, none up to 8), two do.  A substep of 3,100 leaves,
-// ms, with the fill: 3.35 and 2.67 (6 fields), 4.79 and 3.56 (8), 6.77 and 4.94
-// (11).  binary32 ran two a SIMD before and is bound by its instructions: it
-// gains from the running sums alone (1.22 and 1.14 ms, 6 fields; 2.13 and
-// 2.12, 11) and loses 4 % with the column in passes; three wavefronts a SIMD
-// (workgroups of 6) lost 10 %.
+// What bounds it in binary64 are the waits for its about 12,700 stencil loads
+// a leaf: L1 holds little of what the wavefronts read at once, and the tiles of
+// the 32 leaves an XCD works on (242 KB each at 11 fields) twice fill its L2, so
+// about 2.6 MB a leaf come from beyond it.  With one wavefront a SIMD (384
+// registers) nothing covered them.  At 256 registers, which the passes of the
+// column and the running sums allow (73 spilled, in the column, at 11 fields, 9
+// at 8, none at 6), two do.  A substep of 3,100 leaves, ms, with the fill: 3.35
+// and 2.67 (6 fields), 4.79 and 3.56 (8), 6.77 and 4.94 (11).  binary32 ran two a
+// SIMD before: it gains from the running sums alone (1.22 and 1.14 ms, 6 fields;
+// 2.13 and 2.12, 11) and loses 4 % with the column in passes; three wavefronts
+// a SIMD (workgroups of 6) lost 10 %.
 // ---------------------------------------------------------------------------
 
 // The flux store of k_step3d_ws: k_step3d_wg's 27 planes and a spare one
