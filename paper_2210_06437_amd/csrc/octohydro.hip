@@ -610,15 +610,16 @@ static bool cfl_in_kernel(const hydro_grid* gr, const StepArgs& a) {
 // leaf's latency per 256 leaves (a CU works on one at a time), k_step and
 // k_step2 take theirs once up to 1024 wavefronts.  Later-stage substep, us,
 // k_leaf against the shape of default_options:
-//   binary64, fields    64 leaves      512          869
-//              6         14.2  39.2   30.3  45.2   61.5  53.2
-//              8         17.5  47.3   37.1  53.1   76.0  63.8
-//             11         22.8  41.5   49.1  56.3   98.4  70.9
-//             13         29.8  41.7   66.5  63.1  128.1  80.2
-//             16         49.2  66.3  136.7  97.7
-//   binary32   6          9.8  27.3   18.2  32.9   39.0  40.0
-//             11         14.9  31.8   29.7  36.6   60.4  47.4
-//             16         20.2  36.6   40.9  44.1   82.8  59.8
+//   binary64, fields    64 leaves      512          834
+//              6         13.2  34.9   27.9  38.4   56.6  44.7
+//              8         15.7  45.8   35.4  51.5   70.2  60.6
+//             11         22.5  38.9   50.4  52.5   99.7  66.7
+//             13         29.9  39.2   67.4  57.8  128.7  75.8
+//             16         47.7  66.0  132.5  97.7
+//   binary32   6          9.1  21.6   17.0  26.9   32.7  32.4
+//              8         11.6  28.1   22.1  30.9   40.1  37.9
+//             11         14.1  26.5   28.4  31.8   57.1  42.5
+//             16         18.5  30.4   39.8  38.3   76.1  55.7
 static int whole_leaf_limit(int dtype, int nf) {
   if (dtype == HYDRO_F64) return nf <= 9 ? 768 : (nf <= 12 ? 512 : 256);
   return nf <= 10 ? 768 : 512;
