@@ -93,7 +93,9 @@ __device__ __forceinline__ constexpr PointLine face_point(int sd, int pu, int pv
 // The Simpson sum ((corners + 4 edges) + 16 centre) / 36.  The products by 4
 // and 16 are exact, so each FMA rounds once, as the addition does; the
 // division is by the reciprocal with Markstein's residual correction, which
-// gives the correctly rounded quotient in 3 instructions.
+// gives the correctly rounded quotient in 3 instructions while the residual is
+// a number: the hardware's division fix-up then puts in the quotients that
+// have none, an infinite sum's (inf - inf) and a zero's sign.
 __device__ __forceinline__ double simpson_edges(double corners, double edges) {
   return fma(4.0, edges, corners);
 }
@@ -103,12 +105,12 @@ __device__ __forceinline__ float simpson_edges(float corners, float edges) {
 __device__ __forceinline__ double simpson_centre(double corners_edges, double centre) {
   const double x = fma(16.0, centre, corners_edges);
   const double q = x * (1.0 / 36.0);
-  return fma(fma(-36.0, q, x), 1.0 / 36.0, q);
+  return __builtin_amdgcn_div_fixup(fma(fma(-36.0, q, x), 1.0 / 36.0, q), 36.0, x);
 }
 __device__ __forceinline__ float simpson_centre(float corners_edges, float centre) {
   const float x = fmaf(16.0f, centre, corners_edges);
   const float q = x * (1.0f / 36.0f);
-  return fmaf(fmaf(-36.0f, q, x), 1.0f / 36.0f, q);
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-36.0f, q, x), 1.0f / 36.0f, q), 36.0f, x);
 }
 template <typename T>
 __device__ __forceinline__ T simpson_close(T corners, T edges, T centre) {

@@ -1,0 +1,63 @@
+"""Values at the ends of the number range in the step kernels."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2210_06437_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2210_06437_amd import binding as hb
+    return torch, hb
+
+
+@pytest.mark.parametrize("form", [0, 1, 2])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_3d_face_flux_that_overflows(env, dtype, form):
+    """A species whose flux overflows the element type leaves infinities where
+    one face of a cell is infinite and the other is not, and NaN where both
+    are, as the quotient of an infinite Simpson sum by 36 is infinite: in all
+    three forms of the 3D step, binary64 the oracle's result, binary32 the
+    same classes of values (the state is binary64's with the species' scale
+    moved to the end of the binary32 range) around the edge where the species
+    falls.  At the other edge binary64's NaN is the difference of two products
+    that overflow, of which binary32 forms one inside an FMA."""
+    torch, hb = env
+    print(f"case overflow dtype {dtype} form {form}", flush=True)
+    base, nf = 4, 7
+    coord = inputs.uniform_leaves(base)
+    X, _, _ = inputs.cell_centres(coord, base)
+    one, zero = np.ones_like(X), np.zeros_like(X)
+    core = inputs.conserved(one, 1e4 * one, zero, zero, 1e6 * one)
+    species = np.where(X < 0.5, 1.0, 0.0)
+    U64 = np.ascontiguousarray(np.concatenate([core[:6], 1e305 * species[None]]))
+    oracle.set_recon(1)
+    try:
+        ref, _ = oracle.step(oracle.Table(coord, base), U64, 1e-8)
+    finally:
+        oracle.set_recon(0)
+    assert np.isinf(ref[6]).any() and np.isnan(ref[6]).any() and np.isfinite(ref[6]).any()
+    U = U64.copy()
+    if dtype == 1:
+        U[6] = 1e36 * species
+    grid = hb.Grid(coord, base, nf, dtype, reconstruction=hb.HYDRO_RECON_3D)
+    old = hb.hydro_get_option(dtype, nf, hb.HYDRO_OPT_3D_WORKGROUP)
+    hb.hydro_set_option(dtype, nf, hb.HYDRO_OPT_3D_WORKGROUP, form)
+    try:
+        dt = torch.tensor([1e-8], dtype=torch.float64, device="cuda")
+        out = grid.empty_state()
+        Ud = torch.from_numpy(U).to("cuda").to(grid.torch_dtype).contiguous()
+        hb.hydro_step(grid, None, Ud, out, dt, 1.0)
+        got = out.double().cpu().numpy()
+    finally:
+        hb.hydro_set_option(dtype, nf, hb.HYDRO_OPT_3D_WORKGROUP, old)
+    if dtype == 0:
+        assert np.array_equal(got, ref, equal_nan=True)
+    else:
+        falls = (X > 0.25) & (X < 0.75)
+        for what in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(what(got[6][falls]), what(ref[6][falls])), what
