@@ -139,15 +139,19 @@ struct Ppm<float> {
 
 // Half the limited slope of cell j from q[j-1], q[j], q[j+1].  The slope is
 // the centred difference, limited to twice the smaller one-sided difference,
-// where those agree in sign, else 0: the centred difference clamped to
-// [2 min(max(dl, dr), 0), 2 max(min(dl, dr), 0)].  Everything is scaled by a
-// quarter of the full span, and scaling by powers of two is exact, so the
-// value is the limiter's own, bit for bit, with no sign test or select.
+// where the product of those differences is positive, else 0.  The product
+// itself decides, as the method states it: it underflows to 0 in the tail of a
+// steep front (differences below about 2^-537), and a NaN makes it no positive
+// number.  Clamped to [0, 1] (an output modifier of the multiply, which takes
+// NaN to 0) and scaled by the largest number it is 0 there and above the
+// smaller difference elsewhere, so it joins the minimum with no compare or
+// select.  Everything is halved: where the product is positive the differences
+// are far above the subnormal range, so the halves are exact.
 __device__ __forceinline__ double half_slope(double qm, double q0, double qp) {
-  const double d4 = 0.25 * (qp - qm);
   const double dl = q0 - qm, dr = qp - q0;
-  const double hi = fmax(fmin(dl, dr), 0.0), lo = fmin(fmax(dl, dr), 0.0);
-  return fmin(fmax(d4, lo), hi);
+  const double d4 = 0.25 * (qp - qm);
+  const double open = fmin(fmax(dl * dr, 0.0), 1.0) * __DBL_MAX__;
+  return copysign(fmin(fmin(open, fmin(fabs(dl), fabs(dr))), fabs(d4)), d4);
 }
 
 // Interface value between cells of values a and b with half slopes ha, hb:

@@ -32,7 +32,7 @@ namespace octohydro {
 // The PPM parabola of the cell at t along a line of tile stride s: its ends
 // at t - s/2 (l) and t + s/2 (r).  Walking the line the other way (stride
 // -s) gives the same two values with l and r exchanged, bit for bit: the
-// limited slopes change sign exactly (or stay +0), the interface values and
+// limited slopes change sign exactly, the interface values and
 // the monotonisation are symmetric in the two ends, and every sum involved
 // is commutative.
 __device__ __forceinline__ void parabola(const double* __restrict__ t, int s, double& l,

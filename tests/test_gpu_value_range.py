@@ -15,6 +15,51 @@ def env():
     return torch, hb
 
 
+def _state(base, nf, what):
+    """Smooth core fields, species of order one, and in the last species (or
+    the field named) values at the end of the range."""
+    rng = np.random.default_rng(nf)
+    w = inputs.random_smooth(inputs.uniform_leaves(base), base, nf=6, seed=nf)
+    extra = [w.U[0] * rng.uniform(0.1, 0.3, size=w.U[0].shape) for _ in range(nf - 6)]
+    U = np.ascontiguousarray(np.concatenate([w.U[:6]] + [e[None] for e in extra]))
+    if what == "tail":  # differences of 2^-600 .. 2^-480: products up to 2^-960
+        U[-1] = 2.0 ** rng.uniform(-600, -480, size=U[-1].shape)
+    elif what == "front":  # a front that falls by many orders of magnitude a cell
+        U[-1] = 2.0 ** rng.uniform(-1000, 0, size=U[-1].shape)
+    else:
+        field, value = {"nan": (nf - 1, np.nan), "inf": (nf - 1, np.inf), "nan E": (4, np.nan)}[what]
+        hit = rng.random(U[field].shape) < 0.002
+        hit[0, 4, 4, 4] = True
+        U[field][hit] = value
+    return w.leaf_coord, U
+
+
+@pytest.mark.parametrize("recon", [0, 1])
+@pytest.mark.parametrize("what", ["tail", "front", "nan", "inf", "nan E"])
+@pytest.mark.parametrize("base,nf", [(2, 7), (2, 11), (10, 7), (10, 11)])
+def test_fp64_limiter_at_the_ends_of_the_range(env, base, nf, what, recon):
+    """The slope is zero wherever the product of the two one-sided differences
+    is not positive: where it underflows to zero, as in the tail of a species'
+    front, and where a neighbour is NaN or both differences are infinite.
+    Batches for each kernel (8 and 1000 leaves), both reconstructions: the
+    oracle's bits, not-a-number where it has one."""
+    torch, hb = env
+    print(f"case base {base} nf {nf} {what} recon {recon}", flush=True)
+    coord, U = _state(base, nf, what)
+    grid = hb.Grid(coord, base, nf, hb.HYDRO_F64, reconstruction=recon)
+    dt = torch.tensor([1e-4], dtype=torch.float64, device="cuda")
+    out = grid.empty_state()
+    hb.hydro_step(grid, None, torch.from_numpy(U).to("cuda"), out, dt, 1.0)
+    oracle.set_recon(recon)
+    try:
+        ref, _ = oracle.step(oracle.Table(coord, base), U, 1e-4)
+    finally:
+        oracle.set_recon(0)
+    got = out.cpu().numpy()
+    assert np.array_equal(got, ref, equal_nan=True), [
+        int((~((g == r) | (np.isnan(g) & np.isnan(r)))).sum()) for g, r in zip(got, ref)]
+
+
 @pytest.mark.parametrize("form", [0, 1, 2])
 @pytest.mark.parametrize("dtype", [0, 1])
 def test_3d_face_flux_that_overflows(env, dtype, form):
