@@ -167,6 +167,15 @@ __device__ __forceinline__ double interface_value(double a, double b, double ha,
 // point of [l, r].  Each replacement is written under its own execution
 // mask: a 64-bit select is two instructions a value, a masked move or FMA
 // one, so this takes 7 instructions where selects took 13.
+// The compiler's hazard logic does not look into the statement, and a lane move
+// (DPP) needs five wait states after a vector compare has written EXEC and two
+// after the register it reads was written.  MOVES_FOLLOW, for code that may
+// place one behind the statement, fills up to five: the two moves, the restore
+// of EXEC and the two of the s_nop.  (Where none follows it is left out: padded
+// everywhere the RK3 step of 65,535 leaves at 11 fields took 12.28 ms instead
+// of 12.15, of 64 leaves 50.8 us instead of 49.6.)  l and r are written before
+// the last input is read, hence no shared registers (&).
+template <bool MOVES_FOLLOW = false>
 __device__ __forceinline__ void monotonise(double c, double& l, double& r) {
   const double dlr = r - l;
   const double e1 = dlr * (6.0 * fma(-0.5, l + r, c)), e2 = dlr * dlr;
@@ -183,9 +192,13 @@ __device__ __forceinline__ void monotonise(double c, double& l, double& r) {
       "v_cmpx_ge_f64_e64 vcc, 0, %[in]\n\t"
       "v_mov_b64 %[l], %[c]\n\t"
       "v_mov_b64 %[r], %[c]\n\t"
-      "s_mov_b64 exec, %[sv]"
-      : [l] "+v"(l), [r] "+v"(r), [sv] "=&s"(saved)
-      : [c] "v"(c), [c3] "v"(c3), [e1] "v"(e1), [e2] "v"(e2), [in] "v"(in)
+      "s_mov_b64 exec, %[sv]\n\t"
+      ".if %[moves_follow]\n\t"
+      "s_nop 1\n\t"
+      ".endif"
+      : [l] "+&v"(l), [r] "+&v"(r), [sv] "=&s"(saved)
+      : [c] "v"(c), [c3] "v"(c3), [e1] "v"(e1), [e2] "v"(e2), [in] "v"(in),
+        [moves_follow] "n"((int)MOVES_FOLLOW)
       : "vcc");
 }
 
@@ -462,17 +475,32 @@ __device__ __forceinline__ int coarse_cell(int oct, int x, int y, int z) {
 constexpr int DPP_XOR1 = 0xB1;
 constexpr int DPP_XOR8 = 0x128;
 
+// Each move brings its own wait states, since the statement in front of it may
+// be monotonise's, which the compiler's hazard logic does not look into: five
+// after a vector write of EXEC, which also covers the two after the write of the
+// register that is moved.
+template <int CTRL>
+__device__ __forceinline__ int dpp_word(int v) {
+  static_assert(CTRL == DPP_XOR1 || CTRL == DPP_XOR8, "the two moves of a 2x2 group");
+  int r;
+  if constexpr (CTRL == DPP_XOR1)
+    asm volatile("s_nop 4\n\tv_mov_b32_dpp %0, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "=v"(r) : "v"(v));
+  else
+    asm volatile("s_nop 4\n\tv_mov_b32_dpp %0, %1 row_ror:8 row_mask:0xf bank_mask:0xf"
+        : "=v"(r) : "v"(v));
+  return r;
+}
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
+  const int lo = dpp_word<CTRL>((int)(unsigned)b), hi = dpp_word<CTRL>((int)(unsigned)(b >> 32));
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) |
                                           (unsigned long long)(unsigned)lo));
 }
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+  return __int_as_float(dpp_word<CTRL>(__float_as_int(v)));
 }
 
 template <typename T, int PLANE>

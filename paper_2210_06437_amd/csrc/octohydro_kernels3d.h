@@ -34,7 +34,9 @@ namespace octohydro {
 // -s) gives the same two values with l and r exchanged, bit for bit: the
 // limited slopes change sign exactly, the interface values and
 // the monotonisation are symmetric in the two ends, and every sum involved
-// is commutative.
+// is commutative.  MOVES_FOLLOW: the caller moves values between lanes by DPP
+// (see monotonise).
+template <bool MOVES_FOLLOW = false>
 __device__ __forceinline__ void parabola(const double* __restrict__ t, int s, double& l,
                                          double& r) {
   const double q0 = t[-2 * s], q1 = t[-s], q2 = t[0], q3 = t[s], q4 = t[2 * s];
@@ -43,12 +45,13 @@ __device__ __forceinline__ void parabola(const double* __restrict__ t, int s, do
   const double h3 = half_slope(q2, q3, q4);
   l = interface_value(q1, q2, h1, h2);
   r = interface_value(q2, q3, h2, h3);
-  monotonise(q2, l, r);
+  monotonise<MOVES_FOLLOW>(q2, l, r);
 }
 
 // binary32: the ends from the differences of the five values (see ppm_push);
 // walking the line the other way changes the sign of every difference and
 // exchanges l and r, so it gives the same two values too.
+template <bool MOVES_FOLLOW = false>
 __device__ __forceinline__ void parabola(const float* __restrict__ t, int s, float& l, float& r) {
   constexpr float C6 = (float)(1.0 / 6.0);
   const float q0 = t[-2 * s], q1 = t[-s], q2 = t[0], q3 = t[s], q4 = t[2 * s];
@@ -669,10 +672,10 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
 #pragma unroll
       for (int f = 0; f < NF_CORE; ++f) {
         const T* q = Gt + f * fsG + t;
-        parabola(q, s0, lo[0][f], hi[0][f]);
-        parabola(q, s1, lo[1][f], hi[1][f]);
-        parabola(q, s2, lo[2][f], hi[2][f]);
-        parabola(q, s3, lo[3][f], hi[3][f]);
+        parabola<true>(q, s0, lo[0][f], hi[0][f]);
+        parabola<true>(q, s1, lo[1][f], hi[1][f]);
+        parabola<true>(q, s2, lo[2][f], hi[2][f]);
+        parabola<true>(q, s3, lo[3][f], hi[3][f]);
       }
 #pragma unroll
       for (int q = 0; q < 8; q += 2) {
@@ -712,10 +715,10 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
     for (int f = NF_CORE; f < NF; ++f) {
       T l0, h0, l1, h1, l2, h2, l3, h3;
       const T* q = Gt + f * fsG + t;
-      parabola(q, s0, l0, h0);
-      parabola(q, s1, l1, h1);
-      parabola(q, s2, l2, h2);
-      parabola(q, s3, l3, h3);
+      parabola<true>(q, s0, l0, h0);
+      parabola<true>(q, s1, l1, h1);
+      parabola<true>(q, s2, l2, h2);
+      parabola<true>(q, s3, l3, h3);
       const T x0 = passive_flux(prev_cell<0>(h0), l1, vl[0], vr[0], ha[0]);
       const T x1 = passive_flux(prev_cell<0>(h1), l0, vl[1], vr[1], ha[1]);
       const T x2 = passive_flux(prev_cell<0>(h2), l3, vl[2], vr[2], ha[2]);
@@ -747,8 +750,8 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
 #pragma unroll
       for (int f = 0; f < NF_CORE; ++f) {
         const T* q = Gt + f * fsG + t;
-        parabola(q, sA, lA[f], hA[f]);
-        parabola(q, sB, lB[f], hB[f]);
+        parabola<true>(q, sA, lA[f], hA[f]);
+        parabola<true>(q, sB, lB[f], hB[f]);
       }
 #pragma unroll
       for (int q = 0; q < (G == 2 ? 4 : 2); q += 2) {
@@ -786,8 +789,8 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
     for (int f = NF_CORE; f < NF; ++f) {
       T lA, hA, lB, hB;
       const T* q = Gt + f * fsG + t;
-      parabola(q, sA, lA, hA);
-      parabola(q, sB, lB, hB);
+      parabola<true>(q, sA, lA, hA);
+      parabola<true>(q, sB, lB, hB);
       if (G == 0) {
         acc[f].xe = passive_flux(prev_cell<0>(hB), lA, vl[0], vr[0], ha[0]) +
                     passive_flux(prev_cell<0>(hA), lB, vl[1], vr[1], ha[1]);
@@ -813,8 +816,8 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
       for (int f = 0; f < NF_CORE; ++f) {
         T lx, hxe, ly, hye;
         const T* q = Gt + f * fsG + t;
-        parabola(q, SX, lx, hxe);
-        parabola(q, SY, ly, hye);
+        parabola<true>(q, SX, lx, hxe);
+        parabola<true>(q, SY, ly, hye);
         XL[f] = prev_cell<0>(hxe); XR[f] = lx;
         YL[f] = prev_cell<1>(hye); YR[f] = ly;
       }
@@ -834,8 +837,8 @@ __device__ __forceinline__ void ws_plane_xy(const Phys<T>& ph, const T* __restri
     for (int f = NF_CORE; f < NF; ++f) {
       T lx, hxe, ly, hye;
       const T* q = Gt + f * fsG + t;
-      parabola(q, SX, lx, hxe);
-      parabola(q, SY, ly, hye);
+      parabola<true>(q, SX, lx, hxe);
+      parabola<true>(q, SY, ly, hye);
       const T cx = passive_flux(prev_cell<0>(hxe), lx, vlx, vrx, hax);
       const T cy = passive_flux(prev_cell<1>(hye), ly, vly, vry, hay);
       Hx[f] = simpson_close(acc[f].xc, acc[f].xe, cx);
