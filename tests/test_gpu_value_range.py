@@ -26,7 +26,7 @@ def _state(base, nf, what):
         U[-1] = 2.0 ** rng.uniform(-600, -480, size=U[-1].shape)
     elif what == "front":  # a front that falls by many orders of magnitude a cell
         U[-1] = 2.0 ** rng.uniform(-1000, 0, size=U[-1].shape)
-    else:
+    elif what != "none":
         field, value = {"nan": (nf - 1, np.nan), "inf": (nf - 1, np.inf), "nan E": (4, np.nan)}[what]
         hit = rng.random(U[field].shape) < 0.002
         hit[0, 4, 4, 4] = True
@@ -106,3 +106,32 @@ def test_3d_face_flux_that_overflows(env, dtype, form):
         falls = (X > 0.25) & (X < 0.75)
         for what in (np.isnan, np.isposinf, np.isneginf):
             assert np.array_equal(what(got[6][falls]), what(ref[6][falls])), what
+
+
+@pytest.mark.parametrize("recon", [0, 1])
+@pytest.mark.parametrize("field", [0, 1, 3, 4, 6])
+@pytest.mark.parametrize("base", [2, 10])
+def test_fp32_not_a_number_reaches_the_fluxes_of_its_cell(env, base, field, recon):
+    """NaN in one field of a cell: every field whose flux depends on it is NaN
+    in the cell and in its six face neighbours (a core field reaches all
+    fields, a species itself), and where that is all of the reconstruction's
+    reach, in no other cell, as in binary64; a core field's sets the status."""
+    torch, hb = env
+    print(f"case base {base} field {field} recon {recon}", flush=True)
+    nf = 7
+    coord, U = _state(base, nf, "none")
+    leaf = np.flatnonzero((coord[:, 1:] == 1).all(1))[0]
+    U[field, leaf, 4, 3, 5] = np.nan
+    grid = hb.Grid(coord, base, nf, hb.HYDRO_F32, reconstruction=recon)
+    dt = torch.tensor([1e-4], dtype=torch.float64, device="cuda")
+    out = grid.empty_state()
+    hb.hydro_step(grid, None, torch.from_numpy(U).to("cuda").float(), out, dt, 1.0)
+    want = np.zeros(U.shape, bool)
+    for z, y, x in ((4, 3, 5), (3, 3, 5), (5, 3, 5), (4, 2, 5), (4, 4, 5), (4, 3, 4), (4, 3, 6)):
+        want[slice(None) if field < 5 else field, leaf, z, y, x] = True
+    got = torch.isnan(out).cpu().numpy()
+    assert got[want].all(), [int((want & ~got)[f].sum()) for f in range(nf)]
+    if recon == 0:
+        assert np.array_equal(got, want)
+    status = hb.HYDRO_E_UNPHYSICAL if field < 5 else hb.HYDRO_OK
+    assert hb.hydro_check_status(grid) == status
