@@ -135,7 +135,10 @@ __device__ __forceinline__ T simpson9(const T (&h)[9]) {
 // sums pair by pair (2 values a field live instead of 9: 206 registers
 // instead of 243 at 11 binary64 fields), and the points' velocities and
 // signal speeds, which each passive field then uses.
-template <typename T, int NF, int D>
+// AHEAD, for a kernel with one wavefront a SIMD, where no other wavefront covers
+// a wait: the ends of all 9 points are formed before the first flux, with no
+// pins, so that their independent loads are in flight together (394 registers).
+template <typename T, int NF, int D, bool AHEAD = false>
 __device__ __forceinline__ void face_flux_3d(const Phys<T>& ph, const T* __restrict__ Gt,
                                              size_t fsG, int tl, T (&H)[NF], bool& bad) {
   constexpr int SD = D == 0 ? 1 : (D == 1 ? TW : TW * TW);
@@ -143,12 +146,29 @@ __device__ __forceinline__ void face_flux_3d(const Phys<T>& ph, const T* __restr
   constexpr int PV[9] = {-1, 1, -1, 1, -1, 1, 0, 0, 0};
   const int tr = tl + SD;
   T ca[NF_CORE], ed[NF_CORE], vl[9], vr[9], ha[9];  // corner and edge sums
+  T EL[AHEAD ? 9 : 1][NF_CORE], ER[AHEAD ? 9 : 1][NF_CORE];
+  if constexpr (AHEAD) {
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+      const PointLine pl = face_point<D>(1, PU[q], PV[q]);
+      const PointLine pr = face_point<D>(-1, PU[q], PV[q]);
+#pragma unroll
+      for (int f = 0; f < NF_CORE; ++f) {
+        EL[q][f] = line_end(Gt + f * fsG + tl, pl.s, pl.right);
+        ER[q][f] = line_end(Gt + f * fsG + tr, pr.s, pr.right);
+      }
+    }
+  }
 #pragma unroll
   for (int p = 0; p < 5; ++p) {  // the points in pairs, the centre alone
     T h[2][NF_CORE];
 #pragma unroll
     for (int i = 0; i < (p < 4 ? 2 : 1); ++i) {
       const int q = 2 * p + i;
+      if constexpr (AHEAD) {
+        core_flux(ph, D, EL[q], ER[q], h[i], vl[q], vr[q], ha[q], bad);
+        continue;
+      }
       const PointLine pl = face_point<D>(1, PU[q], PV[q]);
       const PointLine pr = face_point<D>(-1, PU[q], PV[q]);
       T UL[NF_CORE], UR[NF_CORE];
@@ -171,7 +191,7 @@ __device__ __forceinline__ void face_flux_3d(const Phys<T>& ph, const T* __restr
       else if (p == 2) ed[f] = h[0][f] + h[1][f];
       else if (p == 3) ed[f] = ed[f] + (h[0][f] + h[1][f]);
       else H[f] = simpson_close(ca[f], ed[f], h[0][f]);
-      keep_order(p < 2 ? ca[f] : (p < 4 ? ed[f] : H[f]));
+      if constexpr (!AHEAD) keep_order(p < 2 ? ca[f] : (p < 4 ? ed[f] : H[f]));
     }
   }
 #pragma unroll
@@ -213,6 +233,13 @@ __device__ __forceinline__ constexpr int tile_at(int x, int y, int z) {
 template <typename T, int NF>
 __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
     k_step3d(StepArgs s, const T* __restrict__ G) {
+  // Binary64 runs one wavefront a SIMD.  Point by point, the compiler keeps 4 to
+  // 7 loads in flight up to 9 fields and 0 to 2 from 10 on, where a wavefront
+  // then waits 58 % of its life (43 % at 9).  Later-stage step of 1,000 leaves,
+  // ms, point by point and with the points' ends formed ahead: 0.98 and 1.06 (8
+  // fields), 1.50 and 1.24 (10), 1.64 and 1.33 (11), 3.21 and 2.52 (12), 3.83
+  // and 2.87 (14), 4.28 and 3.13 (16).
+  constexpr bool AHEAD = sizeof(T) == 8 && NF >= 10;
   __shared__ double hx8[NF * 64];  // x-face 8 of row (y, z), at z * 8 + y
   __shared__ double hy8[NF * 64];  // y-face 8 of column (x, z), at z * 8 + x
   const GridArgs& g = s.g;
@@ -254,8 +281,9 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
       const bool first = zl < 0;
       const int z = z0 + zl;
       T H[NF];
-      face_flux_3d<T, NF, 0>(ph, Gt, fsG, first ? tile_at(SUB - 1, x, y) : tile_at(x - 1, y, z),
-                             H, bad);
+      face_flux_3d<T, NF, 0, AHEAD>(
+          ph, Gt, fsG, first ? tile_at(SUB - 1, x, y) : tile_at(x - 1, y, z), H,
+          bad);
       if (first) {
         if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 0, SUB, x, y, H);
 #pragma unroll
@@ -277,8 +305,9 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
       const bool first = zl < 0;
       const int z = z0 + zl;
       T H[NF];
-      face_flux_3d<T, NF, 1>(ph, Gt, fsG, first ? tile_at(x, SUB - 1, y) : tile_at(x, y - 1, z),
-                             H, bad);
+      face_flux_3d<T, NF, 1, AHEAD>(
+          ph, Gt, fsG, first ? tile_at(x, SUB - 1, y) : tile_at(x, y - 1, z), H,
+          bad);
       if (first) {
         if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 1, SUB, x, y, H);
 #pragma unroll
@@ -298,7 +327,7 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
     for (int zl = zs; zl < 4; ++zl) {
       const int z = z0 + zl;
       T H[NF];
-      face_flux_3d<T, NF, 2>(ph, Gt, fsG, tile_at(x, y, z), H, bad);
+      face_flux_3d<T, NF, 2, AHEAD>(ph, Gt, fsG, tile_at(x, y, z), H, bad);
       if (zl < 0) {
         if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 2, 0, x, y, H);
 #pragma unroll
@@ -342,8 +371,9 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
     const bool first = z < 0;
     T H[NF];
     double sxy[NF];
-    face_flux_3d<T, NF, 0>(ph, Gt, fsG, first ? tile_at(SUB - 1, x, y) : tile_at(x - 1, y, z),
-                           H, bad);
+    face_flux_3d<T, NF, 0, AHEAD>(
+        ph, Gt, fsG, first ? tile_at(SUB - 1, x, y) : tile_at(x - 1, y, z), H,
+        bad);
     if (first) {
       if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 0, SUB, x, y, H);
 #pragma unroll
@@ -358,8 +388,9 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
         sxy[f] = hi - lo;
       }
     }
-    face_flux_3d<T, NF, 1>(ph, Gt, fsG, first ? tile_at(x, SUB - 1, y) : tile_at(x, y - 1, z),
-                           H, bad);
+    face_flux_3d<T, NF, 1, AHEAD>(
+        ph, Gt, fsG, first ? tile_at(x, SUB - 1, y) : tile_at(x, y - 1, z), H,
+        bad);
     if (first) {
       if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 1, SUB, x, y, H);
 #pragma unroll
@@ -374,7 +405,7 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
         sxy[f] = sxy[f] + (hi - lo);
       }
     }
-    face_flux_3d<T, NF, 2>(ph, Gt, fsG, tile_at(x, y, z), H, bad);
+    face_flux_3d<T, NF, 2, AHEAD>(ph, Gt, fsG, tile_at(x, y, z), H, bad);
     if (first) {
       if (g.reg) record_faces<T, NF, 0, NF>(g, leaf, 2, 0, x, y, H);
 #pragma unroll

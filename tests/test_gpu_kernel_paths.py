@@ -359,3 +359,36 @@ def test_cfl_minimum_left_by_the_step_is_that_of_a_pass(env, n_leaves, nf, dtype
     hb.hydro_cfl_dt(grid, out, 0.0, ref[1:])
     got, want = dt[1].item(), ref[1].item()
     assert got == want and got > 0.0, (got, want)
+
+
+@pytest.mark.parametrize("nf", [6, 9, 10, 11, 13, 16])
+def test_3d_one_wavefront_form_matches_the_oracle(env, nf):
+    """The 3D form with one wavefront a leaf on both sides of the field count
+    from which it forms the points' states ahead, a later stage with rotation:
+    the oracle's bits."""
+    torch, hb = env
+    print(f"case 3D one wavefront nf {nf}", flush=True)
+    w = inputs.blobs(base=2, max_level=2, threshold=0.5)
+    U = _species(w, nf, nf)
+    grid = hb.Grid(w.leaf_coord, w.base, nf, hb.HYDRO_F64, omega=0.7,
+                   reconstruction=hb.HYDRO_RECON_3D)
+    T = oracle.Table(w.leaf_coord, w.base)
+    U0 = U * 1.01
+    old = hb.hydro_get_option(0, nf, hb.HYDRO_OPT_3D_WORKGROUP)
+    hb.hydro_set_option(0, nf, hb.HYDRO_OPT_3D_WORKGROUP, 0)
+    try:
+        dt = torch.tensor([1e-4], dtype=torch.float64, device="cuda")
+        out = grid.empty_state()
+        hb.hydro_step(grid, torch.from_numpy(U0).to("cuda"), torch.from_numpy(U).to("cuda"), out,
+                      dt, 0.25)
+        got = out.cpu().numpy()
+    finally:
+        hb.hydro_set_option(0, nf, hb.HYDRO_OPT_3D_WORKGROUP, old)
+    oracle.set_recon(1)
+    oracle.set_omega(0.7)
+    try:
+        ref, bad = oracle.step(T, U, 1e-4, beta=0.25, U0=U0)
+    finally:
+        oracle.set_recon(0)
+        oracle.set_omega(0.0)
+    assert bad == 0 and np.array_equal(got, ref)
