@@ -340,10 +340,12 @@ const char* hydro_last_error(void);
 
 /*
  * Launch options of the fused substep kernel for one (dtype, n_fields) pair;
- * the defaults follow the type and the field count.  Small batches (a few
- * hundred leaves, by type and field count) give each leaf a workgroup of
- * six wavefronts instead, whatever the register budget and the wavefronts
- * per leaf.  The autotuner (paper_2210_06437_amd/autotune.py) times the
+ * the defaults follow the type, the field count and the batch size.  Small
+ * batches (a few hundred leaves, by type and field count) give each leaf a
+ * workgroup of six wavefronts instead, whatever the register budget and the
+ * wavefronts per leaf.  The binary32 kernels that leave the CFL minimum of up
+ * to 13 fields (6 with one wavefront per leaf) keep to the registers of three
+ * waves per SIMD whatever the budget.  The autotuner (paper_2210_06437_amd/autotune.py) times the
  * choices and records the fastest; the Python binding applies its recorded
  * choices at import.
  *   HYDRO_OPT_WAVES_PER_SIMD  1 or 2: register budget of the kernel (2 waves

@@ -606,29 +606,49 @@ static bool cfl_in_kernel(const hydro_grid* gr, const StepArgs& a) {
 }
 
 // Batch size up to which each leaf gets a workgroup of its own (k_leaf) and
-// the launch shape of the options does not apply.  A k_leaf substep takes one
-// leaf's latency per 256 leaves (a CU works on one at a time), k_step and
-// k_step2 take theirs once up to 1024 wavefronts.  Later-stage substep, us,
-// k_leaf against the shape of default_options:
-//   binary64, fields    64 leaves      512          834
-//              6         13.2  34.9   27.9  38.4   56.6  44.7
-//              8         15.7  45.8   35.4  51.5   70.2  60.6
-//             11         22.5  38.9   50.4  52.5   99.7  66.7
-//             13         29.9  39.2   67.4  57.8  128.7  75.8
-//             16         47.7  66.0  132.5  97.7
-//   binary32   6          9.1  21.6   17.0  26.9   32.7  32.4
-//              8         11.6  28.1   22.1  30.9   40.1  37.9
-//             11         14.1  26.5   28.4  31.8   57.1  42.5
-//             16         18.5  30.4   39.8  38.3   76.1  55.7
+// the launch shape of the options does not apply.  The CUs take the leaves of a
+// k_leaf substep one each, so its time steps up every 256 leaves; k_step and
+// k_step2 take one leaf's latency up to 1024 wavefronts.  Later-stage substep,
+// us, k_leaf against the shape that the batch has otherwise:
+//   binary64, fields    64 leaves      216          512          575
+//              6         13.2  34.9   14.0  35.1   25.2  35.9   37.1  36.3
+//              8         15.7  45.9   17.1  46.4   33.6  47.9   48.3  48.2
+//             10         20.0  37.8   21.7  38.1   40.5  45.1   58.6  46.2
+//             12         23.8  39.4   26.5  40.6   53.1  53.7   74.7  54.9
+//             14         34.0  42.5   40.0  43.5   88.0  68.3
+//             16         46.6  60.0   58.9  65.6  127.1  90.0
+//   binary32   8         10.8  25.2   10.9  25.5   19.8  27.6   26.2  29.0
+//              9         11.5  23.0   11.9  23.3   22.2  26.1   30.7  27.8
+//             12         14.7  24.5   15.0  24.8   28.3  29.7   41.1  33.3
+//             16         18.5  27.3   18.7  27.6   37.1  35.3   53.5  40.1
+// Between: 258 leaves 57.0 53.5 (binary64, 13), 47.7 50.5 (12), 34.7 31.7
+// (binary32, 16), 29.0 28.2 (13; 441 leaves 29.3 29.7); 729 and 771 leaves 27.2
+// 29.5 and 34.4 30.8 (binary32, 8).  15 binary64 fields, whose other shape spills
+// nothing: 106 leaves 46.0 50.1, 125 leaves 51.8 50.4.
 static int whole_leaf_limit(int dtype, int nf) {
-  if (dtype == HYDRO_F64) return nf <= 9 ? 768 : (nf <= 12 ? 512 : 256);
-  return nf <= 10 ? 768 : 512;
+  if (dtype == HYDRO_F64) return nf <= 12 ? 512 : (nf == 15 ? 112 : 256);
+  return nf <= 8 ? 768 : (nf <= 13 ? 512 : 256);
+}
+
+// Launch shape of a batch.  Up to 1024 leaves one wavefront a leaf leaves each of
+// the 1024 SIMDs one at most; with 7 to 9 binary64 fields the species then go to a
+// second wavefront unless the options ask for another shape than the default.
+// Later-stage substep, us, with one and two wavefronts a leaf, 1000 leaves: 47.7
+// and 45.7 (7 fields), 55.5 and 50.5 (8), 64.8 and 53.0 (9); 1042 leaves: 66.8 and
+// 84.4, 76.5 and 88.0, 89.0 and 91.8.
+static StepShape step_shape(const Options& o, int dtype, int nf, int blocks) {
+  if (dtype == HYDRO_F64 && nf >= 7 && nf <= 9 && blocks <= 1024) {
+    const Options d = default_options(dtype, nf);
+    if (o.waves_per_simd == d.waves_per_simd && o.waves_per_leaf == d.waves_per_leaf)
+      return StepShape{1, 2};
+  }
+  return StepShape{o.waves_per_simd, o.waves_per_leaf};
 }
 
 static hipError_t launch_step(StepArgs a, int dtype, int blocks, hipStream_t st) {
   const Options o = get_options(dtype, a.g.nf);
   if (a.remap) a.remap = o.xcd_remap;
-  const StepShape sh{o.waves_per_simd, o.waves_per_leaf};
+  const StepShape sh = step_shape(o, dtype, a.g.nf, blocks);
   if (a.dt_next && a.node_out) return hipErrorInvalidValue;  // no kernel does both
   if (blocks <= whole_leaf_limit(dtype, a.g.nf)) {
     const int mode = a.dt_next ? STEP_CFL : (a.node_out ? STEP_RESTRICT : STEP_PLAIN);

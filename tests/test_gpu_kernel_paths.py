@@ -392,3 +392,84 @@ def test_3d_one_wavefront_form_matches_the_oracle(env, nf):
         oracle.set_recon(0)
         oracle.set_omega(0.0)
     assert bad == 0 and np.array_equal(got, ref)
+
+
+def _box_refined_at(base, n_refined):
+    """A box of base^3 sub-grids, its first n_refined in Morton order refined."""
+    coord = inputs.uniform_leaves(base)
+    rows = []
+    for i, (_, x, y, z) in enumerate(coord[inputs.morton_order(coord)]):
+        if i < n_refined:
+            rows += [(1, 2 * x + (q & 1), 2 * y + (q >> 1 & 1), 2 * z + (q >> 2)) for q in range(8)]
+        else:
+            rows.append((0, x, y, z))
+    coord = np.array(rows, np.int32)
+    return np.ascontiguousarray(coord[inputs.morton_order(coord)])
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("nf", range(6, 17))
+@pytest.mark.parametrize("base,n_refined", [(3, 1), (5, 2), (6, 2), (8, 1), (8, 18), (10, 1),
+                                            (10, 15)])
+def test_default_shapes_in_every_mode(env, base, n_refined, nf, dtype):
+    """A chained, rotating RK3 step on octrees of 34, 139, 230, 519, 638, 1007
+    and 1105 leaves, on both sides of every batch size at which the launch
+    shape changes, for every field count: the first two substeps leave the
+    node copies, the last the CFL minimum, as the options of an untouched
+    process have it.  Binary64 the oracle's bits; binary32 within its rounding
+    over the three stages, and the minimum is that of the state it leaves."""
+    torch, hb = env
+    coord = _box_refined_at(base, n_refined)
+    print(f"case {len(coord)} leaves nf {nf} dtype {dtype}", flush=True)
+    w = inputs.random_smooth(coord, base, nf=6, seed=nf)
+    U = _species(w, nf, nf)
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    Un = torch.from_numpy(U).to("cuda").to(tdt).contiguous()
+    grid = hb.Grid(coord, base, nf, dtype, omega=0.3, cfl_epilogue=True)
+    assert grid.c.n_nodes
+    W1, W2, out = (grid.empty_state() for _ in range(3))
+    dt = torch.zeros(2, dtype=torch.float64, device="cuda")
+    hb.hydro_cfl_dt(grid, Un, 0.0, dt[1:])
+    hb.hydro_rk3_step(grid, Un, W1, W2, out, 0.4, dt)
+    assert hb.hydro_check_status(grid) == hb.HYDRO_OK
+    got = out.double().cpu().numpy()
+    T = oracle.Table(coord, base)
+    oracle.set_omega(0.3)
+    try:
+        ref, dt_o, bad = oracle.rk3_step(T, Un.double().cpu().numpy(), 0.4)
+    finally:
+        oracle.set_omega(0.0)
+    assert bad == 0 and dt[0].item() == dt_o
+    if dtype == 0:
+        assert np.array_equal(got, ref)
+    else:
+        top = np.abs(ref).reshape(nf, -1).max(1)
+        assert np.all(np.abs(got - ref).reshape(nf, -1).max(1) < 1e-5 * top)
+    assert dt[1].item() == oracle.cfl_dt(T, got, 1.0)
+
+
+@pytest.mark.parametrize("nf,waves,leaf_waves", [(8, 1, 1), (9, 1, 1), (9, 2, 2)])
+def test_another_shape_than_the_default_below_1024_leaves(env, nf, waves, leaf_waves):
+    """A shape other than the default's, set at 8 and 9 binary64 fields, takes
+    the place of the batch's own: the options read back, and the result is the
+    oracle's."""
+    torch, hb = env
+    print(f"case nf {nf} waves {waves} {leaf_waves}", flush=True)
+    coord = _box_refined_at(10, 1)
+    w = inputs.random_smooth(coord, 10, nf=6, seed=nf)
+    U = _species(w, nf, nf)
+    grid = hb.Grid(coord, 10, nf, hb.HYDRO_F64)
+    keys = (hb.HYDRO_OPT_WAVES_PER_SIMD, hb.HYDRO_OPT_WAVES_PER_LEAF)
+    old = [hb.hydro_get_option(0, nf, k) for k in keys]
+    try:
+        for k, v in zip(keys, (waves, leaf_waves)):
+            hb.hydro_set_option(0, nf, k, v)
+            assert hb.hydro_get_option(0, nf, k) == v
+        dt = torch.tensor([1e-4], dtype=torch.float64, device="cuda")
+        out = grid.empty_state()
+        hb.hydro_step(grid, None, torch.from_numpy(U).to("cuda"), out, dt, 1.0)
+        ref, bad = oracle.step(oracle.Table(coord, 10), U, 1e-4)
+        assert bad == 0 and np.array_equal(out.cpu().numpy(), ref)
+    finally:
+        for k, v in zip(keys, old):
+            hb.hydro_set_option(0, nf, k, v)
