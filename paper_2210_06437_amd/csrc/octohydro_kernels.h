@@ -1567,10 +1567,12 @@ __global__ void __launch_bounds__(384, sizeof(T) == 4 && NF <= 8 ? 3 : 2) k_leaf
     const int off = d == 0 ? b * L::PLANE + a * L::PITCH
                            : (d == 1 ? b * L::PLANE + a : NF * L::FIELD + b * L::PITCH + a);
     const int step = d == 0 ? 1 : (d == 1 ? L::PITCH : L::PLANE);
-    // whole (see k_step) while nothing spills: 8 leaves, us, rolled and whole,
+    // whole (see k_step) where that is faster: 8 leaves, us, rolled and whole,
     // 17.2 and 15.6 (binary64, 8 fields), 21.7 and 21.3 (11; 512 leaves 49.2
-    // and 52.7), 27.7 and 30.0 (13), 14.4 and 13.8 (binary32, 11)
-    constexpr int U = sizeof(T) == 4 || NF <= 9 ? 5 : 1;
+    // and 52.7), 27.7 and 30.0 (13), 14.4 and 13.8 (binary32, 11); 10 binary64
+    // fields, 64 leaves 20.4 and 19.2, 512 leaves 43.3 and 42.8 (12 spilled
+    // registers when whole)
+    constexpr int U = sizeof(T) == 4 || NF <= 10 ? 5 : 1;
 #pragma unroll U
     for (int kk = 5; kk < 10; ++kk) {
       const int k = k0 + kk;
