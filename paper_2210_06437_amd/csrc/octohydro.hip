@@ -379,10 +379,6 @@ static int grid_blocks(int64_t work, int threads, int cap) {
 }
 
 // Ghost fill (hydro_fill_ghosts) into materialised tiles.
-// One workgroup of FILL_THREADS per leaf (65,535 leaves of 11 fields, binary64
-// and binary32: 256 threads 5.74 and 2.96 ms, 512 5.81 and 3.06, 1024 6.19 and
-// 3.53).
-constexpr int FILL_THREADS = 256;
 // The cells of a tile in the order of their sources: region by region (the
 // leaf, then the 26 neighbours), each in the order of its cells in memory, so
 // that consecutive threads read consecutive cells of one block.
@@ -420,25 +416,27 @@ static __device__ const FillOrder fill_order;
 // binary32 3.86 -> 2.96 ms; 5,628 leaves of 11 binary64 fields 447 -> 334 us,
 // 6,966 of 8 binary32 267 -> 157 us.  The fields in groups over the grid, for
 // a smaller working set in L2, were slower (2 groups 5.89 ms, 4 groups 6.41,
-// 11 groups 8.56), and so were ordinary stores (6.06 ms).  The tile stores are non-temporal: nothing here reads a tile again,
-// and L2 is left to the neighbour cells that other tiles read.
-constexpr int FILL_SLOTS = (TILE + FILL_THREADS - 1) / FILL_THREADS;
+// 11 groups 8.56), and so were ordinary stores (6.06 ms).  The tile stores are
+// non-temporal: nothing here reads a tile again, and L2 is left to the neighbour
+// cells that other tiles read.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-template <typename T>
-__global__ void __launch_bounds__(FILL_THREADS) k_fill(GridArgs g, const T* __restrict__ U,
-                                              T* __restrict__ G, int remap, int wide) {
+template <typename T, int THREADS>
+__global__ void __launch_bounds__(THREADS) k_fill(GridArgs g, const T* __restrict__ U,
+                                                  T* __restrict__ G, int remap, int wide,
+                                                  int fields) {
+  constexpr int SLOTS = (TILE + THREADS - 1) / THREADS;
   __shared__ __align__(16) T tile[2][TILE];
   const int leaf = leaf_of_block(blockIdx.x, g.n_leaves, remap);
   const int4 c4 = reinterpret_cast<const int4*>(g.coord)[leaf];
   const int ic[3] = {c4.y, c4.z, c4.w};
   const int blocks = g.base << c4.x;
   const size_t fsU = (size_t)g.n_leaves * CELLS, fsG = (size_t)g.n_leaves * TILE;
-  uint32_t src[FILL_SLOTS];  // cell index within a field array
-  int dst[FILL_SLOTS];       // tile cell; with bit 16 set where 8 cells are averaged
+  uint32_t src[SLOTS];  // cell index within a field array
+  int dst[SLOTS];       // tile cell; with bit 16 set where 8 cells are averaged
 #pragma unroll
-  for (int j = 0; j < FILL_SLOTS; ++j) {
-    const int i = threadIdx.x + j * FILL_THREADS;
+  for (int j = 0; j < SLOTS; ++j) {
+    const int i = threadIdx.x + j * THREADS;
     const int t = fill_order.cell[i < TILE ? i : TILE - 1];
     const int tp[3] = {t % TW, (t / TW) % TW, t / (TW * TW)};
     int r[3], l[3];
@@ -469,20 +467,22 @@ __global__ void __launch_bounds__(FILL_THREADS) k_fill(GridArgs g, const T* __re
     }
   }
   T* __restrict__ Gl = G + (size_t)leaf * TILE;
-  T v[FILL_SLOTS];
-  for (int f = 0; f <= g.nf; ++f) {
-    if (f > 0) {
+  T v[SLOTS];
+  // the workgroup's fields: `fields` of them, or what is left in the last group
+  const int f0 = blockIdx.y * fields, f1 = min(f0 + fields, g.nf);
+  for (int f = f0; f <= f1; ++f) {
+    if (f > f0) {
       // field f - 1, gathered before, goes into its LDS tile
       T* tl = tile[f & 1];
 #pragma unroll
-      for (int j = 0; j < FILL_SLOTS; ++j)
-        if (j + 1 < FILL_SLOTS || threadIdx.x + j * FILL_THREADS < TILE) tl[dst[j] & 0xFFFF] = v[j];
+      for (int j = 0; j < SLOTS; ++j)
+        if (j + 1 < SLOTS || threadIdx.x + j * THREADS < TILE) tl[dst[j] & 0xFFFF] = v[j];
       __syncthreads();
     }
-    if (f < g.nf) {
+    if (f < f1) {
       const T* __restrict__ u = U + f * fsU;
 #pragma unroll
-      for (int j = 0; j < FILL_SLOTS; ++j) {
+      for (int j = 0; j < SLOTS; ++j) {
         const T* __restrict__ P = u + src[j];
         if (dst[j] >> 16)
           v[j] = T(0.125) * (((P[0] + P[1]) + (P[8] + P[9])) + ((P[64] + P[65]) + (P[72] + P[73])));
@@ -490,16 +490,16 @@ __global__ void __launch_bounds__(FILL_THREADS) k_fill(GridArgs g, const T* __re
           v[j] = P[0];
       }
     }
-    if (f > 0) {
+    if (f > f0) {
       const T* tl = tile[f & 1];
       T* out = Gl + (f - 1) * fsG;
       if (wide) {
         constexpr int N = 16 / sizeof(T);
-        for (int i = threadIdx.x; i < TILE / N; i += FILL_THREADS)
+        for (int i = threadIdx.x; i < TILE / N; i += THREADS)
           __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(tl)[i],
                                       reinterpret_cast<u32x4*>(out) + i);
       } else {
-        for (int i = threadIdx.x; i < TILE; i += FILL_THREADS)
+        for (int i = threadIdx.x; i < TILE; i += THREADS)
           __builtin_nontemporal_store(tl[i], out + i);
       }
     }
@@ -509,19 +509,47 @@ __global__ void __launch_bounds__(FILL_THREADS) k_fill(GridArgs g, const T* __re
 // Ghosted 14^3 tiles of U into G (all 26 ghost regions).
 // Leaves go to the XCDs in contiguous Morton ranges (remap mode 1), so that a
 // tile's neighbour cells are mostly read on the XCD that reads them for the
-// neighbour's own tile: 8.12 -> 7.85 ms per binary64 fill of the 65535-leaf
-// case (binary32 unchanged).
+// neighbour's own tile.
 constexpr int FILL_REMAP = 1;
-static int fill_launch(const hydro_grid* gr, const void* U, void* G, hipStream_t st) {
-  const GridArgs g = grid_args(gr);
+// Threads per leaf and groups of fields, each group a workgroup of its own.  A
+// workgroup's two LDS tiles (44 KB in binary64) let a CU hold three, so up to
+// about 4,000 leaves, whose state the L2s hold, 512 threads cover more of a
+// load's wait than 256; beyond, the memory is the limit and the fewer leaves in
+// flight have their neighbours in L2.  Up to 384 leaves, with a leaf or two a CU,
+// two groups halve the fields that a workgroup takes one after another.  Uniform
+// boxes, us, 256 threads, 512, and 512 in two groups:
+//   leaves           64              216              512            1,000
+//   binary64  6  10.7  8.4  7.6  11.6  9.6  9.2  18.5 16.3 16.5  33.6 30.9 31.3
+//            11  14.6 11.9  8.4  18.5 16.2 14.9  31.8 29.2 28.6  58.8 57.4 52.4
+//            16  18.5 15.5 10.1  25.4 23.4 22.0  43.2 40.7 40.2  85.4 84.2 76.7
+//   binary32  6   9.7  7.6  7.5  10.1  7.8  7.4  11.9 10.0 11.1  20.7 18.1 20.9
+//            11  12.9 10.0  7.6  13.4 10.5  9.1  20.0 16.8 17.0  32.9 30.2 30.8
+//   (343 leaves, 11 binary64 fields: 27.2 26.0 22.2, 6 binary32: 11.7 9.8 9.6)
+// and 256 and 512 threads at 4,096 leaves: 109 and 106, 201 and 196, 300 and 297;
+// 8,000: 205 and 203, 665 and 678, 980 and 1004 (binary32 6 fields 112 and 119);
+// 65,535 leaves of 11 fields 5.74 and 5.81 ms, 2.96 and 3.06 in binary32 (1024
+// threads: 6.19 and 3.53).
+constexpr int FILL_WIDE_LEAVES = 4096;
+constexpr int FILL_GROUPED_LEAVES = 384;
+
+template <typename T, int THREADS>
+static void fill_kernel(const GridArgs& g, const void* U, void* G, hipStream_t st) {
   // tiles are multiples of 16 bytes, so G's own alignment decides
   const int wide = (reinterpret_cast<uintptr_t>(G) & 15) == 0;
-  if (gr->dtype == HYDRO_F64)
-    hipLaunchKernelGGL(k_fill<double>, dim3(g.n_leaves), dim3(FILL_THREADS), 0, st, g,
-                       static_cast<const double*>(U), static_cast<double*>(G), FILL_REMAP, wide);
+  const int groups = g.n_leaves <= FILL_GROUPED_LEAVES ? 2 : 1;
+  hipLaunchKernelGGL((k_fill<T, THREADS>), dim3(g.n_leaves, groups), dim3(THREADS), 0, st, g,
+                     static_cast<const T*>(U), static_cast<T*>(G), FILL_REMAP, wide,
+                     (g.nf + groups - 1) / groups);
+}
+
+static int fill_launch(const hydro_grid* gr, const void* U, void* G, hipStream_t st) {
+  const GridArgs g = grid_args(gr);
+  if (g.n_leaves <= FILL_WIDE_LEAVES)
+    gr->dtype == HYDRO_F64 ? fill_kernel<double, 512>(g, U, G, st)
+                           : fill_kernel<float, 512>(g, U, G, st);
   else
-    hipLaunchKernelGGL(k_fill<float>, dim3(g.n_leaves), dim3(FILL_THREADS), 0, st, g,
-                       static_cast<const float*>(U), static_cast<float*>(G), FILL_REMAP, wide);
+    gr->dtype == HYDRO_F64 ? fill_kernel<double, 256>(g, U, G, st)
+                           : fill_kernel<float, 256>(g, U, G, st);
   HIP_TRY(hipGetLastError());
   return HYDRO_OK;
 }

@@ -473,3 +473,28 @@ def test_another_shape_than_the_default_below_1024_leaves(env, nf, waves, leaf_w
     finally:
         for k, v in zip(keys, old):
             hb.hydro_set_option(0, nf, k, v)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("nf", [6, 7, 16])
+@pytest.mark.parametrize("base,n_refined", [(1, 0), (7, 5), (7, 7), (16, 0), (16, 1)])
+def test_ghost_fill_on_both_sides_of_its_batch_sizes(env, base, n_refined, nf, dtype):
+    """Tiles of 1, 378, 392, 4,096 and 4,103 leaves: fields in two groups, an odd
+    count among them, 512 and 256 threads a leaf.  Binary64 the oracle's bits;
+    binary32 within a rounding of each mean, whose operands are within a few
+    per cent of each other, and of one addition in its sum."""
+    torch, hb = env
+    coord = _box_refined_at(base, n_refined)
+    print(f"case {len(coord)} leaves nf {nf} dtype {dtype}", flush=True)
+    tdt = torch.float64 if dtype == 0 else torch.float32
+    rng = np.random.default_rng(nf)
+    U = torch.from_numpy(rng.uniform(1.0, 1.1, size=(nf, len(coord), 8, 8, 8))).to("cuda").to(tdt)
+    grid = hb.Grid(coord, base, nf, dtype)
+    G = torch.full((nf, len(coord), 14, 14, 14), -7.0, dtype=tdt, device="cuda")
+    hb.hydro_fill_ghosts(grid, U.contiguous(), G)
+    want = oracle.fill_ghosts(oracle.Table(coord, base), U.double().cpu().numpy())
+    got = G.double().cpu().numpy()
+    if dtype == 0:
+        assert np.array_equal(got, want)
+    else:
+        assert np.abs(got - want).max() <= 3e-7 * 1.1
