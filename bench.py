@@ -472,7 +472,7 @@ def main():
     # dominant kernel per launch over its measured duration
     roof = {"bound": "hbm", "achieved": hbm_ach / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s",
             "frac": hbm_ach / HBM_PEAK, "traffic": traffic,
-            "kernel": "k_step<double,11> (fused substep, later-stage form)",
+            "kernel": "k_step2<double,11> (fused substep, later-stage form)",
             "kernel_ms": kms64, "bytes_per_launch": byts,
             "target_frac": 0.6}
     # the kernel's second ceiling: operations of the method's evaluation

@@ -377,8 +377,9 @@ const char* hydro_last_error(void);
  *                             lines common to the x- and y-faces once for
  *                             both, and using both ends of its parabola
  *                             (2, the default)
- * Every choice computes the same bits.  Options are process-wide and take effect at the next launch (a captured
- * graph keeps the kernel it was captured with).  Host only, thread-safe.
+ * Every choice computes the same bits.  Options are process-wide and take
+ * effect at the next launch (a captured graph keeps the kernel it was captured
+ * with).  Host only, thread-safe.
  */
 #define HYDRO_OPT_WAVES_PER_SIMD 1
 #define HYDRO_OPT_XCD_REMAP 2

@@ -2,8 +2,8 @@
 
 The library's translation units (host code and small kernels; the fused
 substep in binary64 and in binary32 storage, with its form for small batches;
-the 3D step, its instantiations spread over eight units; the table builder) are compiled to objects in
-parallel and linked into one shared library.
+the 3D step, its instantiations spread over eight units; the table builder) are
+compiled to objects in parallel and linked into one shared library.
 """
 from __future__ import annotations
 

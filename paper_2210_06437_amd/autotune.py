@@ -96,9 +96,7 @@ def tune_workload(torch, w, dtype, reps=5):
     # taken (the last substep's kernel, or a pass over its output), where the
     # node copies are made (left by the substeps, or a pass before each), and
     # the register budget again, since the kernels that take the CFL minimum
-    # or leave the node copies need more registers than the plain one (binary32
-    # at 11 fields: 271 for the CFL variant against 248, one wavefront per SIMD
-    # instead of two unless held to 256)
+    # or leave the node copies need more registers than the plain one
     step_grid = hb.Grid(w.leaf_coord, w.base, w.nf, dtype, cfl_epilogue=True)
     X = torch.from_numpy(w.U).to("cuda").to(tdt).contiguous()
     Y, W1, W2 = step_grid.empty_state(), step_grid.empty_state(), step_grid.empty_state()

@@ -22,8 +22,11 @@
 // header) is evaluated so that the binary64 path of the axis scheme and of the
 // 3D one reproduces a plain sequential evaluation, every operation rounded once,
 // bit for bit: an FMA stands only where its product is exact or inside a
-// division or root whose result is correctly rounded.  In binary32 products
-// and sums are fused and the recurrence carries differences, which rounds less.
+// division or root whose result is correctly rounded.  (A product by one half or
+// two is exact but for sums below 2^-1021, where a result may be a unit of
+// 2^-1074 off, and for values within a few binades of overflow.)  In binary32
+// products and sums are fused and the recurrence carries differences, which
+// rounds less.
 //
 // Layout in HBM: structure of arrays, field-major: U[f][leaf][z][y][x].
 // One 64-lane wavefront owns one leaf in k_step, in two z-halves: lanes
@@ -161,7 +164,8 @@ __global__ void __launch_bounds__(256) k_cfl(GridArgs g, const T* __restrict__ U
     double m = part[0];
     for (int i = 1; i < (int)(blockDim.x >> 6); ++i) m = fmin(m, part[i]);
     // positive doubles order like their bit patterns
-    atomicMin(reinterpret_cast<unsigned long long*>(dt), (unsigned long long)__double_as_longlong(m));
+    atomicMin(reinterpret_cast<unsigned long long*>(dt),
+              (unsigned long long)__double_as_longlong(m));
   }
 }
 
@@ -651,8 +655,8 @@ static bool cfl_in_kernel(const hydro_grid* gr, const StepArgs& a) {
 //             16         18.5  27.3   18.7  27.6   37.1  35.3   53.5  40.1
 // Between: 258 leaves 57.0 53.5 (binary64, 13), 47.7 50.5 (12), 34.7 31.7
 // (binary32, 16), 29.0 28.2 (13; 441 leaves 29.3 29.7); 729 and 771 leaves 27.2
-// 29.5 and 34.4 30.8 (binary32, 8).  15 binary64 fields, whose other shape spills
-// nothing: 106 leaves 46.0 50.1, 125 leaves 51.8 50.4.
+// 29.5 and 34.4 30.8 (binary32, 8).  15 binary64 fields, of which the other shape
+// spills 15 registers and this one 112: 106 leaves 46.0 50.1, 125 leaves 51.8 50.4.
 static int whole_leaf_limit(int dtype, int nf) {
   if (dtype == HYDRO_F64) return nf <= 12 ? 512 : (nf == 15 ? 112 : 256);
   return nf <= 8 ? 768 : (nf <= 13 ? 512 : 256);
@@ -1058,7 +1062,8 @@ int hydro_step_per_leaf(const hydro_grid* gr, const void* U0, const void* Uk, vo
   }
   // pool streams start after the work already queued on `stream`
   HIP_TRY(hipEventRecord(g_pool.events[0], st));
-  for (int i = 0; i < n_streams; ++i) HIP_TRY(hipStreamWaitEvent(g_pool.streams[i], g_pool.events[0], 0));
+  for (int i = 0; i < n_streams; ++i)
+    HIP_TRY(hipStreamWaitEvent(g_pool.streams[i], g_pool.events[0], 0));
   a.remap = 0;
   for (int leaf = 0; leaf < gr->n_leaves; ++leaf) {
     a.leaf_base = leaf;

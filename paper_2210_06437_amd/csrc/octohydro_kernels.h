@@ -151,7 +151,7 @@ __device__ __forceinline__ double half_slope(double qm, double q0, double qp) {
   const double dl = q0 - qm, dr = qp - q0;
   const double d4 = 0.25 * (qp - qm);
   const double open = fmin(fmax(dl * dr, 0.0), 1.0) * __DBL_MAX__;
-  return copysign(fmin(fmin(open, fmin(fabs(dl), fabs(dr))), fabs(d4)), d4);
+  return copysign(fmin(open, fmin(fmin(fabs(dl), fabs(dr)), fabs(d4))), d4);
 }
 
 // Interface value between cells of values a and b with half slopes ha, hb:
@@ -249,9 +249,10 @@ __device__ __forceinline__ float limited_slope2(float d, float dl, float dr) {
 // on interface values rounds the mean of two cell values first.  A median of a
 // NaN takes the other operands, so a NaN goes to its own cell's ends only, not
 // to those of the neighbours.  14 instructions per value instead
-// of about 45 with compares and selects: with the fused face flux below, the later-stage substep of 65,535 leaves
-// and 11 fields went from 2.89 to 2.24 ms, 5,832 leaves of 7 fields from 284
-// to 142 us, the 3D step of 6,966 leaves and 8 fields from 2.16 to 1.44 ms.
+// of about 45 with compares and selects: with the fused face flux below, the
+// later-stage substep of 65,535 leaves and 11 fields went from 2.89 to 2.24 ms,
+// 5,832 leaves of 7 fields from 284 to 142 us, the 3D step of 6,966 leaves and 8
+// fields from 2.16 to 1.44 ms.
 __device__ __forceinline__ void ppm_push(Ppm<float>& s, float qn, int k, float& UL, float& UR) {
   constexpr float C6 = (float)(1.0 / 6.0);
   float dn = 0.0f, dm_new = 0.0f, rc = 0.0f, cl_new = 0.0f, Lc = 0.0f, Rc = 0.0f;
@@ -293,7 +294,9 @@ struct Phys {
 // Internal energy density from the entropy tracer, tau^gamma (dual-energy
 // switch).  Kept out of line: the branch is rare and the inlined pow would
 // hold registers in the hot loop.
-static __device__ __noinline__ double tau_energy(double tau, double gamma) { return pow(tau, gamma); }
+static __device__ __noinline__ double tau_energy(double tau, double gamma) {
+  return pow(tau, gamma);
+}
 static __device__ __noinline__ float tau_energy(float tau, float gamma) { return powf(tau, gamma); }
 
 // rinv = 1/rho, p, c for conserved state (rho, sx, sy, sz, E, tau).
@@ -738,7 +741,8 @@ struct FieldView {
 };
 
 __device__ __forceinline__ double bload(double, const FieldView& v, uint32_t o) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(v.r, (int)o, (int)v.fo, 0));
+  return __builtin_bit_cast(double,
+                            __builtin_amdgcn_raw_buffer_load_b64(v.r, (int)o, (int)v.fo, 0));
 }
 __device__ __forceinline__ float bload(float, const FieldView& v, uint32_t o) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(v.r, (int)o, (int)v.fo, 0));
@@ -872,7 +876,6 @@ __device__ __forceinline__ void core_flux(const Phys<float>& ph, int d,
 // leaf from its Uk.  The lane's place goes through fresh() so that the
 // coordinates are worked out here and not kept through the stream loops of
 // every run, rotating or not.
-__device__ __forceinline__ int fresh(int v);
 __device__ __forceinline__ void rotating_source(const GridArgs& g, const LeafInfo& li, int x,
                                                 int y, double rho, double sx, double sy,
                                                 double (&src)[4]) {
@@ -1061,7 +1064,7 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
     if (k + 1 < TW) load_position<T, NF>(S, pencil_src(p, k + 1), qnext);
     T H[NF];
     stream_step<T, NF>(ph, d, st, qn, H, bad);
-    if (g.reg && (k == 5 || k == TW - 1)) 
+    if (g.reg && (k == 5 || k == TW - 1))
       record_faces<T, NF, 0, NF>(g, li.leaf, d, k - 5, a, 4 * h + zz, H);
     if (k >= 6) {
       const int i = k - 6;  // interior cell along d: H now is its high face
@@ -1085,8 +1088,8 @@ __device__ __forceinline__ void phase_xy(const StepArgs& s, const Phys<T>& ph, c
 // stream loop (see k_step).
 template <typename T, int NF, int MODE, int ZU, int AP>
 __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, const LeafInfo& li,
-                                        double* __restrict__ acc, int h, int lane, double dt, double inv_dx, bool& bad,
-                                        double& speed, int lnode) {
+                                        double* __restrict__ acc, int h, int lane, double dt,
+                                        double inv_dx, bool& bad, double& speed, int lnode) {
   const GridArgs& g = s.g;
   const size_t fs = (size_t)g.n_leaves * CELLS;
   const uint32_t fs_b = (uint32_t)(fs * sizeof(T));
@@ -1128,7 +1131,7 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
     }
     T H[NF];
     stream_step<T, NF>(ph, 2, st, qn, H, bad);
-    if (g.reg && (k == 5 || k == TW - 1)) 
+    if (g.reg && (k == 5 || k == TW - 1))
       record_faces<T, NF, 0, NF>(g, li.leaf, 2, k - 5, x, y, H);
     if (kk >= 6) {
       const int i = k - 6;  // interior cell along z
@@ -1144,9 +1147,9 @@ __device__ __forceinline__ void phase_z(const StepArgs& s, const Phys<T>& ph, co
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
         const double sum = acc[f * L::HALF + ai] + ((double)H[f] - Hprev[f]);
-        const T o = finish_cell<T>(s, FieldView{UO, f * fs_b}, leaf_at + i * 64, st[f].qy, u0v[f], sum,
-                                   rot && f >= 1 && f <= 4, f >= 1 && f <= 4 ? src[f - 1] : 0.0,
-                                   dt, inv_dx);
+        const T o = finish_cell<T>(s, FieldView{UO, f * fs_b}, leaf_at + i * 64, st[f].qy, u0v[f],
+                                   sum, rot && f >= 1 && f <= 4,
+                                   f >= 1 && f <= 4 ? src[f - 1] : 0.0, dt, inv_dx);
         if (f < NF_CORE) cv[f] = o;
         if constexpr (MODE == STEP_RESTRICT) {
           if (lnode >= 0)
@@ -1428,7 +1431,7 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
     T H[NG];
     group_step<T, F0, NG>(ph, 2, st, qn, H, spd, sn & 1, lane, bad);
     ++sn;
-    if (g.reg && (k == 5 || k == TW - 1)) 
+    if (g.reg && (k == 5 || k == TW - 1))
       record_faces<T, NF, F0, NG>(g, li.leaf, 2, k - 5, x, y, H);
     if (kk >= 6) {
       const int i = k - 6;  // interior cell along z
@@ -1443,8 +1446,8 @@ __device__ __forceinline__ void phase_z_group(const StepArgs& s, const Phys<T>& 
       for (int f = 0; f < NG; ++f) {
         const int fg = F0 + f;
         const double sum = acc[fg * ACC_HALF + ai] + ((double)H[f] - Hprev[f]);
-        const T o = finish_cell<T>(s, FieldView{UO, fg * fs_b}, leaf_at + i * 64, st[f].qy, u0v[f], sum,
-                                   rot && fg >= 1 && fg <= 4,
+        const T o = finish_cell<T>(s, FieldView{UO, fg * fs_b}, leaf_at + i * 64, st[f].qy,
+                                   u0v[f], sum, rot && fg >= 1 && fg <= 4,
                                    fg >= 1 && fg <= 4 ? src[fg - 1] : 0.0, dt, inv_dx);
         if (F0 == 0 && f < NF_CORE) cv[f] = o;
         if constexpr (MODE == STEP_RESTRICT) {

@@ -132,9 +132,8 @@ __device__ __forceinline__ T simpson9(const T (&h)[9]) {
 // Flux of all fields through the face between tile cells tl and tl + stride
 // of D (Gt: field 0's tile of the leaf, field stride fsG).  The core fields'
 // ends give the points' Kurganov-Tadmor fluxes, which go into running Simpson
-// sums pair by pair (2 values a field live instead of 9: 206 registers
-// instead of 243 at 11 binary64 fields), and the points' velocities and
-// signal speeds, which each passive field then uses.
+// sums pair by pair (2 values a field live instead of 9), and the points'
+// velocities and signal speeds, which each passive field then uses.
 // AHEAD, for a kernel with one wavefront a SIMD, where no other wavefront covers
 // a wait: the ends of all 9 points are formed before the first flux, with no
 // pins, so that their independent loads are in flight together (394 registers).
@@ -351,8 +350,8 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 2 : 1)
         const double sum = acc3[f * 256 + zl * 64 + lane] + ((double)H[f] - hz3[f * 64 + lane]);
         hz3[f * 64 + lane] = (double)H[f];
         const T u0 = s.U0 ? static_cast<const T*>(s.U0)[(size_t)f * fs + at] : T(0);
-        finish_cell<T>(s, FieldView{UO, f * fs_b}, at, ukc[f * fsG], u0, sum, rot && f >= 1 && f <= 4,
-                       f >= 1 && f <= 4 ? src[f - 1] : 0.0, dt, inv_dx);
+        finish_cell<T>(s, FieldView{UO, f * fs_b}, at, ukc[f * fsG], u0, sum,
+                       rot && f >= 1 && f <= 4, f >= 1 && f <= 4 ? src[f - 1] : 0.0, dt, inv_dx);
       }
     }
   }
@@ -616,7 +615,7 @@ __global__ void __launch_bounds__(256, 1) k_step3d_wg(StepArgs s, const T* __res
 // the 32 leaves an XCD works on (242 KB each at 11 fields) twice fill its L2, so
 // about 2.6 MB a leaf come from beyond it.  With one wavefront a SIMD (384
 // registers) nothing covered them.  At 256 registers, which the passes of the
-// column and the running sums allow (73 spilled, in the column, at 11 fields, 9
+// column and the running sums allow (75 spilled, in the column, at 11 fields, 9
 // at 8, none at 6), two do.  A substep of 3,100 leaves, ms, with the fill: 3.35
 // and 2.67 (6 fields), 4.79 and 3.56 (8), 6.77 and 4.94 (11).  binary32 ran two a
 // SIMD before: it gains from the running sums alone (1.22 and 1.14 ms, 6 fields;
@@ -1182,8 +1181,11 @@ constexpr int ws_waves() {
   return sizeof(T) == 8 ? 8 : 4;
 }
 template <typename T, int NF>
-__global__ void __launch_bounds__((64 * ws_waves<T, NF>()),
-                                  (sizeof(T) == 8 || 2 * ws3d_lds_bytes<T, NF>() <= 160 * 1024 ? 2 : 1))
+constexpr int ws_waves_per_simd() {
+  return sizeof(T) == 8 || 2 * ws3d_lds_bytes<T, NF>() <= 160 * 1024 ? 2 : 1;
+}
+template <typename T, int NF>
+__global__ void __launch_bounds__((64 * ws_waves<T, NF>()), (ws_waves_per_simd<T, NF>()))
     k_step3d_ws(StepArgs s, const T* __restrict__ G) {
   __shared__ T Hs[WS_PLANES][NF][64];  // the layout of k_step3d_wg and a spare plane
   const GridArgs& g = s.g;
@@ -1220,7 +1222,8 @@ __global__ void __launch_bounds__((64 * ws_waves<T, NF>()),
     else ws_column_carry<T, NF>(g, ph, Gt, fsG, leaf, c0, c1, lane, Hs, bad);
   }
 #pragma unroll 1
-  for (int z = z0; z <= z1; z += ws_waves<T, NF>() == 8 ? 4 : 1) ws_plane_xy<T, NF>(ph, Gt, fsG, z, lane, Hs, bad);
+  for (int z = z0; z <= z1; z += ws_waves<T, NF>() == 8 ? 4 : 1)
+    ws_plane_xy<T, NF>(ph, Gt, fsG, z, lane, Hs, bad);
 #pragma unroll 1
   for (int k = k0; k <= k1; k += 2) ws_boundary<T, NF>(g, ph, Gt, fsG, leaf, k, lane, Hs, bad);
   if (g.status && __any(bad) && lane == 0) atomicOr(g.status, (int)HYDRO_STATUS_UNPHYSICAL);
@@ -1241,7 +1244,8 @@ hipError_t launch_step3d_one(const StepArgs& a, int blocks, const T* G, int wg, 
   }
   if constexpr (ws3d_lds_bytes<T, NF>() <= 160 * 1024) {
     if (wg == 2) {
-      hipLaunchKernelGGL((k_step3d_ws<T, NF>), dim3(blocks), dim3((64 * ws_waves<T, NF>())), 0, st, a, G);
+      hipLaunchKernelGGL((k_step3d_ws<T, NF>), dim3(blocks), dim3((64 * ws_waves<T, NF>())), 0, st,
+                         a, G);
       return hipGetLastError();
     }
   }
